@@ -38,7 +38,7 @@ struct MlpL {
 
 struct WsPlan {
   size_t erecv, chunk, unit_r, nunits, V, V16, PROJ, AGG, ES, DV[2], DAGG, DZS, DE, DEL_E[3], HID_E[2], DEL_N[3], HID_N[2],
-      HID_NK, HID_E1, PART, VPART, SRANGE, total;
+      HID_NK, HID_E1, PART, VPART, SRANGE, PSH, total;
   int64_t max_units;
   // edge-stream checkpointing: interval s (0: every block kept), checkpoints
   bool lean = false;
@@ -47,6 +47,8 @@ struct WsPlan {
   bool infer = false;
   // node projections kept per block (row-split kernels, every block kept)
   bool proj_all = false;
+  // fp32 row-split edge kernels (edge_f32)
+  bool f32 = false;
   // blocks k >= h1_first keep their first-Linear ReLU output (HID_E1 slot k - h1_first)
   int h1_first = 0;
   // receiver / edge boundaries of the backward's edge chunks
@@ -291,7 +293,17 @@ WsPlan make_plan(const mgn_model* m, const mgn_graph* g) {
   // (row-split kernels: for the last h1_stash blocks only, as memory allows;
   // the others recompute it from e and the kept projections)
   p.HID_E1 = nh1 > 0 ? take(ts * (size_t)nh1 * ne * L) : 0;
+  // fp32 row-split edge kernels: the projections take rows that are free while
+  // the edge half of a block runs (P_r: the block's aggregates, stored after
+  // they are read; P_s: the backward's per-sender sums, or, forward-only, the
+  // next node latents and rows of their own for the halo)
+  p.f32 = edge_f32(m->prec, m->L, m->D);
   if (p.infer) {
+    const size_t psh = p.f32 ? al(4 * (size_t)g->n_halo * L) : 0;
+    // a graph that fits the static workspace of mgn_forward_noalloc without
+    // those halo rows only keeps the streaming kernel, so that it still runs
+    if (psh > 0 && o <= MGN_NOALLOC_WS_MAX && o + psh > MGN_NOALLOC_WS_MAX) p.f32 = false;
+    else p.PSH = take(psh);
     p.total = o;
     return p;
   }
@@ -619,6 +631,20 @@ hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p,
     e = launch_node_proj(L, v16, no + nh, ea.mlp.lin[0], proj, st);
     if (e != hipSuccess) return e;
   }
+  if (p.f32) {
+    float* ps = p.infer ? (float*)(ws + p.V) + (size_t)((k + 1) & 1) * no * L : (float*)(ws + p.DZS);
+    float* ps_halo = p.infer ? (float*)(ws + p.PSH) : ps + (size_t)no * L;
+    {
+      Timed t_(m, MGN_T_NODE_PROJ, st);
+      e = launch_node_proj_f32(L, v, ea.H, no, nh, ea.mlp.lin[0], ps, ps_halo, agg, st);
+      if (e != hipSuccess) return e;
+    }
+    ea.ps = ps;
+    ea.ps_halo = ps_halo;
+    ea.pr = agg;
+    Timed t_(m, MGN_T_EDGE_FWD, st);
+    return launch_edge_fwd_f32(L, D, ea, g.n_edges, st);
+  }
   Timed t_(m, MGN_T_EDGE_FWD, st);
   return launch_edge_fwd(m->prec, L, D, ea, FWD_EDGE_GRID, st);
 }
@@ -762,7 +788,9 @@ mgn_status fwd_begin(mgn_model* m, const mgn_graph* g, const float* nf, const fl
   {
     Timed t_(m, MGN_T_OTHER, st);
     e = launch_erecv(g->row_ptr, no, (int32_t*)(b.ws + p.erecv), st);
-    if (e == hipSuccess)
+    // work units: for the streaming edge kernels only (the others give each
+    // wave a receiver-aligned range of its own)
+    if (e == hipSuccess && !p.f32 && !edge_rs(m->prec, L, D) && !edge_rsb(m->prec, L, D))
       e = launch_plan(g->row_ptr, no, 4 * te, 4 * te, (int32_t*)(b.ws + p.chunk), (int32_t*)(b.ws + p.unit_r),
                       (int32_t*)(b.ws + p.nunits), st);
   }
@@ -1086,7 +1114,7 @@ struct Bwd {
         a.e_base = e0;
         {
           Timed t_(m, MGN_T_EDGE_BWD, st);
-          e = launch_edge_bwd(m->prec, L, D, a, BWD_GRID, st);
+          e = p.f32 ? launch_edge_bwd_f32(L, D, a, rows, st) : launch_edge_bwd(m->prec, L, D, a, BWD_GRID, st);
         }
         CHK("edge block");
         e = run_vec(m, ml, d_params, acc, st, edge_bwd_grid(m->prec, L, D, BWD_GRID));

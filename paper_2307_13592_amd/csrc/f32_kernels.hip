@@ -1,0 +1,639 @@
+// fp32 T-form kernels (gfx950): the edge half of a block with its first
+// Linear split by rows, and the node projections that go with it.
+//
+// The first Linear acts on [e | v_s | v_r]; its sender and receiver column
+// blocks are applied once per node (node_proj_f32_kernel), so per edge
+// z_1 = W_e e + P_s[s] + P_r[r] takes L x L products instead of 3L x L.  All
+// products are computed transposed (Y^T = W X^T): a weight fragment is the
+// MFMA A operand, a 16-row tile of activations the B operand.  With
+// v_mfma_f32_16x16x4_f32 lane (e, q) supplies one k value of row e per
+// instruction; taking the four values 16 kg + 4 q + r (r = 0..3) of a 16-byte
+// chunk in four instructions makes one layout serve everywhere: the packed
+// weights (lane (i, q): W[16 cb + i][16 kg + 4 q ..]), rows in memory in plain
+// column order (16 bytes per lane and 16-column block), and the accumulators,
+// which hold columns 16 cb + 4 q + r of row e and so are the next product's B
+// operand as they stand.  One wave works alone on 16-edge tiles of its own
+// receiver-aligned range; the per-edge weights sit in LDS.
+#include <hip/hip_runtime.h>
+
+#include "kernels.h"
+#include "tform.h"
+
+namespace mgn {
+
+namespace {
+
+// Waves per workgroup: two per SIMD.  The fp32 MFMA and the vector ALU take
+// turns (the counters show a 16-edge tile's matrix cycles and its vector
+// instructions adding up), so more waves hide nothing more: at l = 128 they
+// spill (12 waves: forward 1.03 ms, backward 1.84 ms on 1.35M edges against
+// 0.89 and 1.25), at l = 64 they cut the ranges finer (16 waves: backward
+// 113 us on 270,000 edges against 101).
+constexpr int TF_NWV = 8, TF_NTH = 64 * TF_NWV;
+
+// Fragment slot of lane (i, q) in a packed 16 x 16 weight block held in LDS:
+// the q-th run of 16 slots, its order XORed with q.  A 16-byte read by all
+// lanes (product with W) is a permutation of each 256-byte run; a 4-byte read
+// of the transposed element order (product with W^T, tf_gemm_t) then touches
+// every bank once.
+__device__ __forceinline__ int tf_slot(int i, int q) { return 16 * q + (i ^ q); }
+
+// Copies NB 16-column blocks x NB k-groups of packed fragments (source block
+// stride SRC k-groups, first k-group kg0) into LDS in tf_slot order, NTH
+// threads, the loads of up to eight fragments per thread in flight.
+template <int NB, int SRC, int NTH>
+__device__ __forceinline__ void tf_copy_frags(void* dst, const uint4* __restrict__ src, int kg0) {
+  constexpr int TOTAL = NB * NB * 64, IT = (TOTAL + NTH - 1) / NTH, U = IT < 8 ? IT : 8;
+  uint4* d = reinterpret_cast<uint4*>(dst);
+  for (int j0 = 0; j0 < IT; j0 += U) {
+    uint4 v[U];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int i = threadIdx.x + (j0 + j) * NTH, blk = i >> 6;
+      if (TOTAL % (NTH * U) == 0 || i < TOTAL) v[j] = src[((blk / NB) * SRC + kg0 + blk % NB) * 64 + (i & 63)];
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int i = threadIdx.x + (j0 + j) * NTH;
+      if (TOTAL % (NTH * U) == 0 || i < TOTAL) d[(i & ~63) + tf_slot(i & 15, (i >> 4) & 3)] = v[j];
+    }
+  }
+}
+
+// acc[cb] (+)= sum over k-groups of W[cb][kg] (LDS) x X[kg].
+template <int NB, bool ZERO = true>
+__device__ __forceinline__ void tf_gemm(const float4* Wl, const float4 (&X)[NB], floatx4 (&acc)[NB], int slot) {
+  if constexpr (ZERO) {
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int kg = 0; kg < NB; ++kg) {
+    float4 w[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) w[cb] = Wl[(cb * NB + kg) * 64 + slot];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[cb].x, X[kg].x, acc[cb], 0, 0, 0);
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[cb].y, X[kg].y, acc[cb], 0, 0, 0);
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[cb].z, X[kg].z, acc[cb], 0, 0, 0);
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[cb].w, X[kg].w, acc[cb], 0, 0, 0);
+  }
+}
+
+// The same with W^T, from the same LDS copy of W: output block cb takes
+// W[16 kg + 4 q + r][16 cb + i], element i % 4 of the slot of lane
+// (4 q + r, i / 4) in block (kg, cb).  tb[r] is that element's index in a block.
+__device__ __forceinline__ void tf_t_index(int i, int q, int (&tb)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) tb[r] = tf_slot(4 * q + r, i >> 2) * 4 + (i & 3);
+}
+template <int NB>
+__device__ __forceinline__ void tf_gemm_t(const float* Wl, const float4 (&X)[NB], floatx4 (&acc)[NB],
+                                          const int (&tb)[4]) {
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kg = 0; kg < NB; ++kg) {
+    const float x[4] = {X[kg].x, X[kg].y, X[kg].z, X[kg].w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float w[NB];
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) w[cb] = Wl[(kg * NB + cb) * 256 + tb[r]];
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[cb], x[r], acc[cb], 0, 0, 0);
+    }
+  }
+}
+
+// A tile's metadata as rt_meta_load, rows past the range end repeating the
+// range's last edge (their results are never used).
+__device__ __forceinline__ RsMetaRaw tf_meta_load(const int32_t* __restrict__ erecv, const int32_t* __restrict__ send,
+                                                  int64_t sb, int64_t e1) {
+  const int64_t e = sb + (threadIdx.x & 15);
+  const int64_t i = e < e1 ? e : e1 - 1;
+  RsMetaRaw w;
+  w.r = erecv[i];
+  w.s = send[i];
+  w.rn = e + 1 < e1 ? erecv[e + 1] : -1;
+  return w;
+}
+__device__ __forceinline__ RsMeta tf_meta_make(const RsMetaRaw& w, int n) {
+  RsMeta mt{w.r, w.s, 0};
+  mt.last = __ballot((int)(threadIdx.x & 15) < n && w.rn != w.r);
+  return mt;
+}
+
+// Ordered receiver sums of a tile's values v (columns 16 cb + 4 q + r of row
+// e): 64 columns at a time through the wave's 2 KiB scratch, 32 of them per
+// half (lanes 0..31, then 32..63), so that two L x L weight matrices leave
+// room for eight waves' scratch at L = 128.  Each lane carries the running sum
+// of column ln + 64 j; a segment's total is stored at its last row.
+template <int L>
+__device__ __forceinline__ void tf_segment_sums(const float4 (&v)[L / 16], float* scr, const RsMeta& mt, int n, int ln,
+                                                float (&run)[L / 64], float* dst) {
+  const int e = ln & 15, q = ln >> 4;
+#pragma unroll
+  for (int j = 0; j < L / 64; ++j) {
+    float x[16];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        *reinterpret_cast<float4*>(scr + rs_sw32<32>(e, c * 16 + q * 4)) = v[4 * j + 2 * half + c];
+      if ((ln >> 5) == half) {
+#pragma unroll
+        for (int row = 0; row < 16; ++row) x[row] = scr[rs_sw32<32>(row, ln & 31)];
+      }
+    }
+#pragma unroll
+    for (int row = 0; row < 16; ++row) {
+      if (row < n) {
+        run[j] += x[row];
+        if ((mt.last >> row) & 1ull) {
+          dst[(int64_t)__builtin_amdgcn_readlane(mt.r, row) * L + ln + 64 * j] = run[j];
+          run[j] = 0.f;
+        }
+      }
+    }
+  }
+}
+
+template <int NB>
+__device__ __forceinline__ float tf_lane_sum(const float4 (&v)[NB]) {
+  float4 t = v[0];
+#pragma unroll
+  for (int cb = 1; cb < NB; ++cb) {
+    t.x += v[cb].x;
+    t.y += v[cb].y;
+    t.z += v[cb].z;
+    t.w += v[cb].w;
+  }
+  return (t.x + t.y) + (t.z + t.w);
+}
+
+// 1 / std of a row whose lane values are y, given its mean.
+template <int NB, int L>
+__device__ __forceinline__ float tf_rstd(const float4 (&y)[NB], float mu, float eps) {
+  float4 d[NB];
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) {
+    const float a = y[cb].x - mu, b = y[cb].y - mu, c = y[cb].z - mu, e = y[cb].w - mu;
+    d[cb] = make_float4(a * a, b * b, c * c, e * e);
+  }
+  return 1.0f / sqrtf(rt_sum4(tf_lane_sum<NB>(d)) / L + eps);
+}
+
+__device__ __forceinline__ float4 tf_add(const floatx4& a, const float4& b) {
+  return make_float4(a[0] + b.x, a[1] + b.y, a[2] + b.z, a[3] + b.w);
+}
+__device__ __forceinline__ float4 tf_relu(const float4& v) {
+  return make_float4(v.x > 0.f ? v.x : 0.f, v.y > 0.f ? v.y : 0.f, v.z > 0.f ? v.z : 0.f, v.w > 0.f ? v.w : 0.f);
+}
+template <int NB>
+__device__ __forceinline__ void tf_load(const float* __restrict__ p, int q, float4 (&v)[NB]) {
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) v[cb] = rt_ld4(p, cb, q);
+}
+template <int NB>
+__device__ __forceinline__ void tf_store(float* p, int q, const float4 (&v)[NB]) {
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) *reinterpret_cast<float4*>(p + cb * 16 + q * 4) = v[cb];
+}
+
+// ------------------------------------------------------------ edge forward ---
+template <int L, int D>
+struct TfFwdLay {
+  static constexpr int NB = L / 16, W = L * L * 4;
+  static constexpr int OFF_VEC = D * W;                 // last bias, gamma, beta[, hidden bias]
+  static constexpr int OFF_SCR = OFF_VEC + (D == 3 ? 4 : 3) * L * 4;
+  static constexpr int SCR = 16 * 32 * 4;
+  static constexpr int END = OFF_SCR + TF_NWV * SCR;
+  static_assert(END <= 160 * 1024, "LDS");
+};
+
+// Forward of one block's edge half.  Bound by the matrix pipe: 4 L^2 flops per
+// edge at 157 TFLOP/s (L = 128, 1.35M edges: 0.56 ms; measured 0.89 ms with
+// the vector instructions between the products, 1.99 ms for the streaming
+// kernel, which applies the whole 3L x L first Linear per edge).  P_r may share its rows with a.agg: a
+// receiver's row is read with its edges' tiles and its sum stored after them,
+// by the same wave.
+template <int L, int D>
+__global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int64_t n_edges, int nact) {
+  using Lay = TfFwdLay<L, D>;
+  constexpr int NB = Lay::NB;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float4* W1 = reinterpret_cast<float4*>(lds);
+  float4* WH = reinterpret_cast<float4*>(lds + Lay::W);
+  float4* WL = reinterpret_cast<float4*>(lds + (D - 1) * Lay::W);
+  float* vbl = reinterpret_cast<float*>(lds + Lay::OFF_VEC);
+  float* vg = vbl + L;
+  float* vbt = vbl + 2 * L;
+  float* vbh = vbl + 3 * L;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  int64_t r0 = 0, r1 = 0, E0 = 0, E1 = 0;
+  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, 0, a.n_owned, 0, n_edges, nact, r0, r1, E0, E1);
+  rs_zero_empty(a.row_ptr, r0, r1, a.agg, L);
+  tf_copy_frags<NB, 3 * NB, TF_NTH>(W1, a.mlp.lin[0].wf, 0);
+  if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
+  tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
+  rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
+  rt_copy_vec(vg, a.mlp.gamma, L);
+  rt_copy_vec(vbt, a.mlp.beta, L);
+  if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
+  __syncthreads();
+  if (E0 >= E1) return;
+  const float* Ein = reinterpret_cast<const float*>(a.Ein);
+  float* Eout = reinterpret_cast<float*>(a.Eout);
+  float* hid = reinterpret_cast<float*>(a.hid_out);
+  float run[L / 64] = {};
+  // e^k rows of a tile are loaded while the tile before runs its last
+  // product, the P rows at the tile's start: they are added after its first
+  // product, which hides them.  So no product waits for a load, nor, through
+  // the in-order memory counter, for the stores issued before it.  Past the
+  // range's end its last edge is read again.
+  float4 ef[NB];
+  auto load_e = [&](int64_t sb, int ln) {
+    tf_load<NB>(Ein + (sb + (ln & 15) < E1 ? sb + (ln & 15) : E1 - 1) * L, ln >> 4, ef);
+  };
+  RsMetaRaw cur = tf_meta_load(a.erecv, a.send, E0, E1);
+  load_e(E0, lane);
+  for (int64_t sb = E0; sb < E1; sb += 16) {
+    int ln = lane;  // an opaque copy: lane-dependent addresses are formed per tile, not kept in registers
+    asm volatile("" : "+v"(ln));
+    const int e = ln & 15, q = ln >> 4, slot = tf_slot(e, q);
+    const int n = (int)(E1 - sb < 16 ? E1 - sb : 16);
+    const bool ok = e < n;
+    const RsMeta mt = tf_meta_make(cur, n);
+    float4 ps[NB], pr[NB];
+    tf_load<NB>(mt.s < a.n_owned ? a.ps + (int64_t)mt.s * L : a.ps_halo + ((int64_t)mt.s - a.n_owned) * L, q, ps);
+    tf_load<NB>(a.pr + (int64_t)mt.r * L, q, pr);
+    cur = tf_meta_load(a.erecv, a.send, sb + 16, E1);
+    __builtin_amdgcn_sched_barrier(0);
+    floatx4 acc[NB];
+    tf_gemm<NB>(W1, ef, acc, slot);
+    float4 h[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      const float4 z = tf_add(acc[cb], ps[cb]);
+      h[cb] = tf_relu(make_float4(z.x + pr[cb].x, z.y + pr[cb].y, z.z + pr[cb].z, z.w + pr[cb].w));
+    }
+    if (hid && ok) tf_store<NB>(hid + (sb + e) * L, q, h);
+    if constexpr (D == 3) {
+      tf_gemm<NB>(WH, h, acc, slot);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vbh, cb, q)));
+    }
+    float4 ek[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) ek[cb] = ef[cb];
+    load_e(sb + 16, ln);
+    __builtin_amdgcn_sched_barrier(0);
+    tf_gemm<NB>(WL, h, acc, slot);
+    float4 y[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) y[cb] = tf_add(acc[cb], rt_ld4(vbl, cb, q));
+    const float mu = rt_sum4(tf_lane_sum<NB>(y)) / L;
+    const float rs = tf_rstd<NB, L>(y, mu, a.eps);
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {  // y becomes m
+      const float4 g = rt_ld4(vg, cb, q), bt = rt_ld4(vbt, cb, q);
+      y[cb].x = g.x * ((y[cb].x - mu) * rs) + bt.x;
+      y[cb].y = g.y * ((y[cb].y - mu) * rs) + bt.y;
+      y[cb].z = g.z * ((y[cb].z - mu) * rs) + bt.z;
+      y[cb].w = g.w * ((y[cb].w - mu) * rs) + bt.w;
+    }
+    if (Eout && ok) {
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb)
+        ek[cb] = make_float4(ek[cb].x + y[cb].x, ek[cb].y + y[cb].y, ek[cb].z + y[cb].z, ek[cb].w + y[cb].w);
+      tf_store<NB>(Eout + (sb + e) * L, q, ek);
+    }
+    tf_segment_sums<L>(y, scr, mt, n, ln, run, a.agg);
+  }
+}
+
+// ----------------------------------------------------------- edge backward ---
+template <int L, int D>
+struct TfBwdLay {
+  static constexpr int NB = L / 16, W = L * L * 4;
+  // the last [and hidden] Linear once each (product and transposed product
+  // read the same copy), then W_e in the backward packing
+  static constexpr int OFF_WH = W, OFF_W1 = (D - 1) * W;
+  static constexpr int OFF_VEC = D * W;                 // last bias, gamma[, hidden bias]
+  static constexpr int OFF_SCR = OFF_VEC + (D == 3 ? 3 : 2) * L * 4;
+  static constexpr int SCR = 16 * 32 * 4;
+  static constexpr int END = OFF_SCR + TF_NWV * SCR;
+  static constexpr int NVEC = (D + 2) * L;              // bias / gamma / beta partials per wave
+  static_assert(END <= 160 * 1024 && TF_NWV * NVEC * 4 <= OFF_SCR, "LDS");
+};
+
+// Backward of one block's edge half, bound by the matrix pipe as the forward
+// (6 L^2 flops per edge; L = 128, 1.35M edges: floor 0.84 ms, measured 1.25 ms,
+// the streaming kernel 3.15 ms with every weight fragment read from L2 for
+// each tile).  It starts from the forward's h_1 (a.hid_in): the
+// layers after the first recomputed, LayerNorm backward, the data gradients
+// down to dz_0, de^k = de^{k+1} + dz_0 W_e, receiver sums of dz_0 over the
+// consumed dagg rows, per-workgroup bias / LayerNorm partials.
+template <int L, int D>
+__global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int64_t n_edges, int nact) {
+  using Lay = TfBwdLay<L, D>;
+  constexpr int NB = Lay::NB, NV = 4 * NB, NR = NV / 16;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float* WL = reinterpret_cast<float*>(lds);
+  float* WH = reinterpret_cast<float*>(lds + Lay::OFF_WH);
+  float4* W1 = reinterpret_cast<float4*>(lds + Lay::OFF_W1);
+  float* vbl = reinterpret_cast<float*>(lds + Lay::OFF_VEC);
+  float* vg = vbl + L;
+  float* vbh = vbl + 2 * L;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  int64_t r0 = a.r_lo, r1 = a.r_lo, E0 = 0, E1 = 0;
+  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, a.r_lo, a.r_hi, a.e_base, n_edges, nact, r0, r1, E0, E1);
+  rs_zero_empty(a.row_ptr, r0, r1, a.dagg, L);
+  tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
+  if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
+  tf_copy_frags<NB, NB, TF_NTH>(W1, a.mlp.lin[0].wb, 0);  // e block: the first NB column blocks
+  rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
+  rt_copy_vec(vg, a.mlp.gamma, L);
+  if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
+  __syncthreads();
+  // column totals of the bias / LayerNorm gradients (rt_col_totals' share of
+  // each lane): gamma, beta, last bias, hidden biases
+  constexpr int NQ = 2 + D;
+  float qacc[NQ][NR];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k)
+#pragma unroll
+    for (int t = 0; t < NR; ++t) qacc[k][t] = 0.f;
+  auto coltot = [&](const float4 (&x)[NB], int k, int e) {
+    float f[NV];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      f[4 * cb] = x[cb].x;
+      f[4 * cb + 1] = x[cb].y;
+      f[4 * cb + 2] = x[cb].z;
+      f[4 * cb + 3] = x[cb].w;
+    }
+    rt_col_totals<NV>(f, e);
+#pragma unroll
+    for (int t = 0; t < NR; ++t) qacc[k][t] += f[t];
+  };
+  const float* hin = reinterpret_cast<const float*>(a.hid_in);
+  const float* dnx = reinterpret_cast<const float*>(a.de_next);
+  float* deo = reinterpret_cast<float*>(a.de_out);
+  float run[L / 64] = {};
+  // h_1 rows of a tile are loaded while the tile before runs its last
+  // product, de^{k+1} (the last block has none: its loads re-read the h_1 rows
+  // and are replaced by zeros) and dagg at the tile's start, used after its
+  // first product (cf. edge_fwd_f32_kernel)
+  float4 h1[NB];
+  auto load_h1 = [&](int64_t sb, int ln) {
+    tf_load<NB>(hin + (sb + (ln & 15) < E1 ? sb + (ln & 15) : E1 - 1) * L, ln >> 4, h1);
+  };
+  RsMetaRaw cur{};
+  if (E0 < E1) {
+    cur = tf_meta_load(a.erecv, a.send, E0, E1);
+    load_h1(E0, lane);
+  }
+  for (int64_t sb = E0; sb < E1; sb += 16) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int e = ln & 15, q = ln >> 4, slot = tf_slot(e, q);
+    const int n = (int)(E1 - sb < 16 ? E1 - sb : 16);
+    const bool ok = e < n;
+    const RsMeta mt = tf_meta_make(cur, n);
+    const int64_t srow = (sb - a.e_base + e) * L;
+    float4 de[NB], dm[NB];
+    tf_load<NB>((dnx ? dnx : hin) + (sb + (ok ? e : n - 1)) * L, q, de);
+    tf_load<NB>(a.dagg + (int64_t)mt.r * L, q, dm);
+    cur = tf_meta_load(a.erecv, a.send, sb + 16, E1);
+    __builtin_amdgcn_sched_barrier(0);
+    uint32_t mask[2] = {0u, 0u};  // ReLU derivative of the hidden layers, bit cb * 4 + r
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      mask[0] |= (h1[cb].x > 0.f ? 1u : 0u) << (4 * cb);
+      mask[0] |= (h1[cb].y > 0.f ? 1u : 0u) << (4 * cb + 1);
+      mask[0] |= (h1[cb].z > 0.f ? 1u : 0u) << (4 * cb + 2);
+      mask[0] |= (h1[cb].w > 0.f ? 1u : 0u) << (4 * cb + 3);
+    }
+    floatx4 acc[NB];
+    if constexpr (D == 3) {
+      tf_gemm<NB>(reinterpret_cast<const float4*>(WH), h1, acc, slot);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        h1[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vbh, cb, q)));
+        mask[1] |= (h1[cb].x > 0.f ? 1u : 0u) << (4 * cb);
+        mask[1] |= (h1[cb].y > 0.f ? 1u : 0u) << (4 * cb + 1);
+        mask[1] |= (h1[cb].z > 0.f ? 1u : 0u) << (4 * cb + 2);
+        mask[1] |= (h1[cb].w > 0.f ? 1u : 0u) << (4 * cb + 3);
+      }
+      if (ok) tf_store<NB>(reinterpret_cast<float*>(a.hid[1]) + srow, q, h1);
+    }
+    tf_gemm<NB>(reinterpret_cast<const float4*>(WL), h1, acc, slot);
+    float4 y[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) y[cb] = tf_add(acc[cb], rt_ld4(vbl, cb, q));
+    const bool has_de = dnx != nullptr;
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      if (!has_de) de[cb] = make_float4(0.f, 0.f, 0.f, 0.f);
+      dm[cb].x = ok ? dm[cb].x + de[cb].x : 0.f;
+      dm[cb].y = ok ? dm[cb].y + de[cb].y : 0.f;
+      dm[cb].z = ok ? dm[cb].z + de[cb].z : 0.f;
+      dm[cb].w = ok ? dm[cb].w + de[cb].w : 0.f;
+    }
+    const float mu = rt_sum4(tf_lane_sum<NB>(y)) / L;
+    const float rs = tf_rstd<NB, L>(y, mu, a.eps);
+    // LayerNorm backward: dy = rstd (dm g - mean(dm g) - xhat mean(dm g xhat))
+    float t1, t2;
+    {
+      float4 d1[NB], d2[NB];
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        const float4 g = rt_ld4(vg, cb, q);
+        y[cb] = make_float4((y[cb].x - mu) * rs, (y[cb].y - mu) * rs, (y[cb].z - mu) * rs, (y[cb].w - mu) * rs);
+        d1[cb] = make_float4(dm[cb].x * g.x, dm[cb].y * g.y, dm[cb].z * g.z, dm[cb].w * g.w);
+        d2[cb] = make_float4(d1[cb].x * y[cb].x, d1[cb].y * y[cb].y, d1[cb].z * y[cb].z, d1[cb].w * y[cb].w);
+      }
+      t1 = rt_sum4(tf_lane_sum<NB>(d1)) / L;
+      t2 = rt_sum4(tf_lane_sum<NB>(d2)) / L;
+    }
+    coltot(dm, 1, e);
+    float4 v[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      const float4 g = rt_ld4(vg, cb, q);
+      v[cb].x = rs * (dm[cb].x * g.x - t1 - y[cb].x * t2);
+      v[cb].y = rs * (dm[cb].y * g.y - t1 - y[cb].y * t2);
+      v[cb].z = rs * (dm[cb].z * g.z - t1 - y[cb].z * t2);
+      v[cb].w = rs * (dm[cb].w * g.w - t1 - y[cb].w * t2);
+      // gamma's column terms
+      dm[cb] = make_float4(dm[cb].x * y[cb].x, dm[cb].y * y[cb].y, dm[cb].z * y[cb].z, dm[cb].w * y[cb].w);
+    }
+    if (ok) tf_store<NB>(reinterpret_cast<float*>(a.delta[D - 1]) + srow, q, v);
+    coltot(dm, 0, e);
+    coltot(v, 2, e);
+    // hidden layers: dz_{j-1} = (dz_j W_j) * [z_{j-1} > 0]
+    int tb[4];
+    tf_t_index(e, q, tb);
+#pragma unroll
+    for (int j = D - 1; j >= 1; --j) {
+      tf_gemm_t<NB>(j == D - 1 ? WL : WH, v, acc, tb);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        const uint32_t mk = mask[j - 1] >> (4 * cb);
+        v[cb] = make_float4(mk & 1u ? acc[cb][0] : 0.f, mk & 2u ? acc[cb][1] : 0.f, mk & 4u ? acc[cb][2] : 0.f,
+                            mk & 8u ? acc[cb][3] : 0.f);
+      }
+      if (ok) tf_store<NB>(reinterpret_cast<float*>(a.delta[j - 1]) + srow, q, v);
+      coltot(v, 2 + j, e);
+    }
+    load_h1(sb + 16, ln);
+    __builtin_amdgcn_sched_barrier(0);
+    // edge-stream gradient: de^k = de^{k+1} + dz_0 W_1[:, e-block]
+    tf_gemm<NB>(W1, v, acc, slot);
+    if (ok) {
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) de[cb] = tf_add(acc[cb], de[cb]);
+      tf_store<NB>(deo + (sb + e) * L, q, de);
+    }
+    tf_segment_sums<L>(v, scr, mt, n, ln, run, a.dagg);
+  }
+  // column partials: lane (e, q)'s totals are columns 16 cb + 4 q + r for
+  // index e * NR + t = 4 cb + r; then the waves in order through LDS (the
+  // weight area is free now)
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(lds);
+  {
+    float* rw = red + wave * Lay::NVEC;
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+      const int i = (lane & 15) * NR + t;
+      const int col = (i >> 2) * 16 + (lane >> 4) * 4 + (i & 3);
+#pragma unroll
+      for (int h = 0; h < D - 1; ++h) rw[h * L + col] = qacc[3 + h][t];
+      rw[(D - 1) * L + col] = qacc[2][t];
+      rw[D * L + col] = qacc[0][t];
+      rw[(D + 1) * L + col] = qacc[1][t];
+    }
+  }
+  __syncthreads();
+  float* vp = a.vpart + (int64_t)blockIdx.x * a.nvec;
+  for (int i = threadIdx.x; i < Lay::NVEC; i += TF_NTH) {
+    float t = 0.f;
+    for (int w = 0; w < TF_NWV; ++w) t += red[w * Lay::NVEC + i];
+    vp[i] = t;
+  }
+}
+
+// --------------------------------------------------------- node projections ---
+// P_s[n] = W_s v_n for the local nodes (owned rows to ps, halo rows to
+// ps_halo) and P_r[n] = W_r v_n + b_1 for the owned ones.  Each workgroup
+// takes one side, so two share a CU's LDS.
+template <int L>
+__global__ __launch_bounds__(TF_NTH) void node_proj_f32_kernel(const float* V, const float* H, int64_t n_owned,
+                                                               int64_t n_halo, Lin w1, float* ps, float* ps_halo,
+                                                               float* pr) {
+  constexpr int NB = L / 16;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float4* W = reinterpret_cast<float4*>(lds);
+  const int side = (blockIdx.x >> 3) & 1;
+  tf_copy_frags<NB, 3 * NB, TF_NTH>(W, w1.wf, (1 + side) * NB);
+  __syncthreads();
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  const int64_t to = (n_owned + 15) / 16, nt = side ? to : to + (n_halo + 15) / 16;
+  const int64_t nblk = gridDim.x >> 1, blk = (blockIdx.x & 7) + 8 * (blockIdx.x >> 4);
+  for (int64_t t = blk + nblk * wave; t < nt; t += nblk * TF_NWV) {
+    int ln = lane;  // opaque: the weight fragments are read per tile, not kept in registers
+    asm volatile("" : "+v"(ln));
+    const int e = ln & 15, q = ln >> 4, slot = tf_slot(e, q);
+    const bool halo = t >= to;
+    const int64_t row0 = (halo ? t - to : t) * 16, rows = halo ? n_halo : n_owned;
+    const int64_t row = row0 + e;
+    const bool ok = row < rows;
+    float4 x[NB];
+    tf_load<NB>((halo ? H : V) + (ok ? row : row0) * L, q, x);
+    floatx4 acc[NB];
+    tf_gemm<NB>(W, x, acc, slot);
+    if (ok) {
+      float* o = (side ? pr : halo ? ps_halo : ps) + row * L;
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        float4 v = make_float4(acc[cb][0], acc[cb][1], acc[cb][2], acc[cb][3]);
+        if (side) v = tf_add(acc[cb], rt_ld4(w1.b, cb, q));
+        *reinterpret_cast<float4*>(o + cb * 16 + q * 4) = v;
+      }
+    }
+  }
+}
+
+template <class F>
+void allow_lds(F* fn, int bytes) {
+  if (bytes > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+// Working waves per workgroup for `edges` edges: as many as give each a
+// 16-edge tile, so that a small graph's tiles are full and lie on SIMDs of
+// their own (a tile's products fill one SIMD's matrix pipe: two short tiles on
+// one SIMD take as long as two full ones).
+int tf_waves(int64_t edges) {
+  const int64_t w = (edges + 16 * RS_GRID - 1) / (16 * RS_GRID);
+  return (int)(w < 1 ? 1 : w < TF_NWV ? w : TF_NWV);
+}
+
+template <int L, int D>
+hipError_t edge_fwd_f32_t(const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st) {
+  using Lay = TfFwdLay<L, D>;
+  allow_lds(edge_fwd_f32_kernel<L, D>, Lay::END);
+  hipLaunchKernelGGL((edge_fwd_f32_kernel<L, D>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
+                     n_edges, tf_waves(n_edges));
+  return hipGetLastError();
+}
+template <int L, int D>
+hipError_t edge_bwd_f32_t(const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st) {
+  using Lay = TfBwdLay<L, D>;
+  allow_lds(edge_bwd_f32_kernel<L, D>, Lay::END);
+  hipLaunchKernelGGL((edge_bwd_f32_kernel<L, D>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
+                     n_edges, tf_waves(n_edges));
+  return hipGetLastError();
+}
+template <int L>
+hipError_t node_proj_f32_t(const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1, float* ps,
+                           float* ps_halo, float* pr, hipStream_t st) {
+  const int64_t tiles = (n_owned + 15) / 16 + (n_halo + 15) / 16;
+  const int64_t g = (tiles + 7) / 8 * 16;  // both sides, multiples of 8 workgroups each
+  hipLaunchKernelGGL((node_proj_f32_kernel<L>), dim3((unsigned)(g < 512 ? g : 512)), dim3(TF_NTH), L * L * 4, st, V, H,
+                     n_owned, n_halo, w1, ps, ps_halo, pr);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool edge_f32(int prec, int L, int D) { return prec == F32 && (L == 64 || (L == 128 && D == 2)); }
+
+hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st) {
+  if (L == 64) return D == 2 ? edge_fwd_f32_t<64, 2>(a, n_edges, st) : edge_fwd_f32_t<64, 3>(a, n_edges, st);
+  if (L == 128 && D == 2) return edge_fwd_f32_t<128, 2>(a, n_edges, st);
+  return hipErrorInvalidValue;
+}
+hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st) {
+  if (!a.hid_in) return hipErrorInvalidValue;
+  if (L == 64) return D == 2 ? edge_bwd_f32_t<64, 2>(a, n_edges, st) : edge_bwd_f32_t<64, 3>(a, n_edges, st);
+  if (L == 128 && D == 2) return edge_bwd_f32_t<128, 2>(a, n_edges, st);
+  return hipErrorInvalidValue;
+}
+hipError_t launch_node_proj_f32(int L, const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1,
+                                float* ps, float* ps_halo, float* pr, hipStream_t st) {
+  if (n_owned + n_halo == 0) return hipSuccess;
+  if (L == 64) return node_proj_f32_t<64>(V, H, n_owned, n_halo, w1, ps, ps_halo, pr, st);
+  if (L == 128) return node_proj_f32_t<128>(V, H, n_owned, n_halo, w1, ps, ps_halo, pr, st);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace mgn

@@ -41,6 +41,9 @@ struct EdgeFwdArgs {
   void* Eout;       // edge latents out, or null (last block)
   float* agg;       // [n_owned][L]
   const float* proj;  // node projections [n_local][2L] (row-split kernels), else unused
+  // fp32 row-split kernels: P_s of the owned and of the halo rows, P_r of the
+  // owned rows (may share its rows with agg); null: the streaming kernel
+  const float *ps, *ps_halo, *pr;
   void* hid_out;      // streaming and row-split kernels: the first Linear's ReLU output [E][L] (storage type) kept for the
                       // backward, or null
   float eps;
@@ -191,6 +194,14 @@ int edge_bwd_grid(int prec, int L, int D, int grid);
 // Whether the edge kernels take the row-split form (it needs the node
 // projections of launch_node_proj for each block).
 bool edge_rs(int prec, int L, int D);
+// fp32 row-split edge kernels and their node projections (f32_kernels.hip):
+// latent 64, or 128 at MLP depth 2.  The forward takes EdgeFwdArgs::ps .. pr;
+// the backward starts from the forward's first-Linear ReLU output (hid_in).
+bool edge_f32(int prec, int L, int D);
+hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st);
+hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st);
+hipError_t launch_node_proj_f32(int L, const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1,
+                                float* ps, float* ps_halo, float* pr, hipStream_t st);
 hipError_t launch_node_proj(int L, const void* v16, int64_t n_local, const Lin& w1, float* proj, hipStream_t st);
 // bf16, l = 256: the edge forward and backward in row-split form with the
 // weights streamed through LDS (the forward, and a backward that recomputes

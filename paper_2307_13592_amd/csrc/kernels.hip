@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
+#include "tform.h"
 #include "../../include/mgn.h"
 
 namespace mgn {
@@ -1532,7 +1533,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(EdgeWpe<L>::
 
 constexpr int RS_NWV = 8;              // waves per workgroup
 constexpr int RS_NTH = 64 * RS_NWV;
-constexpr int RS_GRID = 256;           // one workgroup per compute unit; a multiple of 8
 
 // bf16 / fp32 element index of (row, col) in a 16-row scratch tile of width
 // L whose 16-byte chunks are XOR-swizzled by row (conflict-free both for
@@ -1542,12 +1542,6 @@ __device__ __forceinline__ int rs_sw16(int row, int col) {
   constexpr int M = (L / 8 < 16 ? L / 8 : 16) - 1;
   return row * L + ((((col >> 3) ^ (row & M))) << 3) + (col & 7);
 }
-template <int L>
-__device__ __forceinline__ int rs_sw32(int row, int col) {
-  constexpr int M = (L / 4 < 16 ? L / 4 : 16) - 1;
-  return row * L + ((((col >> 2) ^ (row & M))) << 2) + (col & 3);
-}
-
 // acc[cb] = sum over k-groups of A[kg] x B[cb][kg]: one 16-row tile, every
 // 16-column block cb, B fragments in LDS ([cb][kg][lane], 16 bytes each).
 template <int NB, int NKG>
@@ -1571,49 +1565,6 @@ __device__ __forceinline__ void rs_copy_frags(uint4* dst, const uint4* __restric
   }
 }
 
-// The wave's index in its workgroup, as a wave-uniform (scalar) value.
-__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-
-// A wave-uniform value held in scalar registers.
-__device__ __forceinline__ int64_t rs_uniform(int64_t x) {
-  const uint64_t u = (uint64_t)x;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Receiver range of wave w (of W waves in total) within [lo_r, hi_r):
-// receiver-aligned, about E / W edges each; the waves of one XCD
-// (blockIdx % 8) get neighbouring ranges.
-__device__ __forceinline__ void rs_range(const int32_t* __restrict__ row_ptr, int64_t lo_r, int64_t hi_r, int64_t& r0,
-                                         int64_t& r1) {
-  const int G = gridDim.x, b = blockIdx.x, nwv = blockDim.x >> 6, wave = wave_id();
-  const int64_t W = (int64_t)G * nwv;
-  const int64_t q = ((int64_t)(b & 7) * (G >> 3) + (b >> 3)) * nwv + wave;
-  const int64_t e0 = row_ptr[lo_r], E = row_ptr[hi_r] - e0;
-  auto find = [&](int64_t target) {  // first receiver r >= lo_r with row_ptr[r] >= target
-    int64_t lo = lo_r, hi = hi_r;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (row_ptr[mid] >= target) hi = mid;
-      else lo = mid + 1;
-    }
-    return lo;
-  };
-  r0 = q == 0 ? lo_r : find(e0 + E * q / W);
-  r1 = q + 1 == W ? hi_r : find(e0 + E * (q + 1) / W);
-}
-
-// Zeroes the rows (width L) of the receivers in [r0, r1) without edges (one
-// wave, a lane per receiver).
-__device__ __forceinline__ void rs_zero_empty(const int32_t* __restrict__ row_ptr, int64_t r0, int64_t r1, float* dst,
-                                              int L) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t r = r0 + lane; r < r1; r += 64)
-    if (row_ptr[r] == row_ptr[r + 1])
-      for (int c = 0; c < L; c += 4) *reinterpret_cast<float4*>(dst + r * L + c) = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-
 // ----------------------------------------------------------------- T form ---
 // The row-split edge kernels and node_proj_kernel compute every product
 // transposed, Y^T = W X^T: weight fragments are the MFMA A operand and a
@@ -1629,35 +1580,6 @@ __device__ __forceinline__ void rs_zero_empty(const int32_t* __restrict__ row_pt
 // instructions).  Column sums over a tile's rows are a reduce-scatter across
 // the 16 lanes of a group (DPP).  Rows in memory keep the plain column order:
 // a lane reads or writes 4 consecutive columns per 16-column block.
-
-// One 16-edge tile's metadata, every lane for its row e = lane & 15: the
-// edge's receiver, sender and the next edge's receiver (-1 past the range
-// end); the mask has bit j (j < 16) set where row j ends a receiver segment.
-// The loads are issued one tile ahead (rt_meta_load) and turned into the
-// mask when the tile starts (rt_meta_make), so no tile waits for them.
-struct RsMeta {
-  int32_t r, s;
-  unsigned long long last;
-};
-struct RsMetaRaw {
-  int32_t r, s, rn;
-};
-__device__ __forceinline__ RsMetaRaw rt_meta_load(const int32_t* __restrict__ erecv, const int32_t* __restrict__ send,
-                                                  int64_t sb, int64_t e1) {
-  const int e = threadIdx.x & 15;
-  RsMetaRaw w{-1, 0, -1};
-  if (sb + e < e1) {
-    w.r = erecv[sb + e];
-    w.s = send[sb + e];
-    if (sb + e + 1 < e1) w.rn = erecv[sb + e + 1];
-  }
-  return w;
-}
-__device__ __forceinline__ RsMeta rt_meta_make(const RsMetaRaw& w) {
-  RsMeta mt{w.r, w.s, 0};
-  mt.last = __ballot(w.r >= 0 && w.rn != w.r);
-  return mt;
-}
 
 // Like rs_copy_frags, with the eight k-slots of every fragment reordered so
 // that slot j of lane group q pairs with k = 32 kg + 16 (j / 4) + 4 q + j % 4:
@@ -1773,65 +1695,6 @@ __device__ __forceinline__ void rt_store_frags(uint16_t* __restrict__ row, int q
   }
 }
 
-// Sum over the four 16-lane groups; every lane gets the same bits.
-__device__ __forceinline__ float rt_sum4(float x) {
-  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  const auto p2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-  return __uint_as_float(p2[0]) + __uint_as_float(p2[1]);
-}
-
-// Per-lane partial over an accumulator tile's values, four chains.
-template <int NB>
-__device__ __forceinline__ float rt_lane_sum(const float (&v)[NB][4]) {
-  float t[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    t[r] = v[0][r];
-#pragma unroll
-    for (int cb = 1; cb < NB; ++cb) t[r] += v[cb][r];
-  }
-  return (t[0] + t[1]) + (t[2] + t[3]);
-}
-
-// One reduce-scatter step within a 16-lane group: v[0, N) -> v[0, N / 2);
-// the lane keeps the half that `hi` selects, summed with the DPP partner's
-// copy of it (the partner keeps the other half).  Both halves' sums are
-// formed, each one add with the partner's value read through DPP (every
-// lane of these patterns has a partner in its row), and one is selected:
-// three instructions per pair instead of two selects, a move and an add.
-template <int N, int CTRL>
-__device__ __forceinline__ void rt_halve(float* v, bool hi) {
-  // no contraction with a product that formed v: both partners must add the
-  // same two rounded values
-#pragma clang fp contract(off)
-#pragma unroll
-  for (int k = 0; k < N / 2; ++k) {
-    const float lo = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[k]), CTRL, 0xf, 0xf, true)) + v[k];
-    const float up =
-        __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[k + N / 2]), CTRL, 0xf, 0xf, true)) + v[k + N / 2];
-    v[k] = hi ? up : lo;
-  }
-}
-
-// Column totals over a tile's 16 rows.  In: v[NV] per lane (index 4 cb + r of
-// the accumulator order).  Out: lane e's v[t], t < NV / 16, is the total of
-// index e * NV / 16 + t.  Partners: row mirror (e ^ 15), half-row mirror
-// (e ^ 7), then e ^ 3 and e ^ 1 within quads.
-template <int NV>
-__device__ __forceinline__ void rt_col_totals(float (&v)[NV], int e) {
-  static_assert(NV >= 16, "at least one total per lane");
-  rt_halve<NV, 0x140>(v, e & 8);
-  rt_halve<NV / 2, 0x141>(v, e & 4);
-  rt_halve<NV / 4, 0x1B>(v, e & 2);
-  rt_halve<NV / 8, 0xB1>(v, e & 1);
-}
-
-// 4 consecutive floats of a plain-order row at column 16 cb + 4 q.
-__device__ __forceinline__ float4 rt_ld4(const float* __restrict__ p, int cb, int q) {
-  return *reinterpret_cast<const float4*>(p + cb * 16 + q * 4);
-}
-
 // z_1 of a tile in T order: W_e e (MFMA) + P_s[s] + P_r[r], added in that
 // order, with b_1 inside P_r (the forward and the recompute in the backward
 // share it).
@@ -1859,11 +1722,6 @@ __device__ __forceinline__ void rt_first_layer(const uint4 (&ef)[L / 32], const 
     z[cb][2] = (z[cb][2] + ps[cb].z) + pr[cb].z;
     z[cb][3] = (z[cb][3] + ps[cb].w) + pr[cb].w;
   }
-}
-
-// Copies n floats into LDS (all threads of the workgroup).
-__device__ __forceinline__ void rt_copy_vec(float* dst, const float* __restrict__ src, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
 }
 
 // Accumulator tile -> bf16 scratch (row order, swizzled) -> A fragments.
@@ -1958,7 +1816,7 @@ __global__ __launch_bounds__((RsFwdLay<L, D>::NTH)) void edge_fwd_rs_kernel(Edge
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   __syncthreads();
   int64_t r0, r1;
-  rs_range(a.row_ptr, 0, a.n_owned, r0, r1);
+  rs_range(a.row_ptr, 0, a.n_owned, r0, r1, blockDim.x >> 6);
   rs_zero_empty(a.row_ptr, r0, r1, a.agg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
@@ -2138,7 +1996,7 @@ __global__ __launch_bounds__(RS_NTH) void edge_bwd_rs_kernel(EdgeBwdArgs a) {
   rt_copy_frags(W1b, a.mlp.lin[0].wb, NB, NKH, NKH, 0);  // e block: the first NB column blocks
   __syncthreads();
   int64_t r0, r1;
-  rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1);
+  rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1, blockDim.x >> 6);
   rs_zero_empty(a.row_ptr, r0, r1, a.dagg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
@@ -2692,7 +2550,7 @@ void edge_fwd_rw_kernel(EdgeFwdArgs a) {
   rt_copy_vec(vbt, a.mlp.beta, L);
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   int64_t r0, r1;
-  rs_range(a.row_ptr, 0, a.n_owned, r0, r1);
+  rs_range(a.row_ptr, 0, a.n_owned, r0, r1, blockDim.x >> 6);
   rs_zero_empty(a.row_ptr, r0, r1, a.agg, L);
   // wave-uniform bounds, kept in scalar registers
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);
@@ -2975,7 +2833,7 @@ void edge_bwd_rw_kernel(EdgeBwdArgs a) {
   rt_copy_vec(vg, a.mlp.gamma, L);
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   int64_t r0, r1;
-  rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1);
+  rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1, blockDim.x >> 6);
   rs_zero_empty(a.row_ptr, r0, r1, a.dagg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const int ntile = rw_max_tiles((int)((E1 - E0 + 15) / 16), reinterpret_cast<int*>(lds + Lay::OFF_SLOT));
@@ -6345,13 +6203,13 @@ hipError_t launch_edge_fwd(int prec, int L, int D, const EdgeFwdArgs& a, int gri
 #define EF(PP, LL, DD) \
   if (prec == PP && L == LL && D == DD) return edge_fwd_t<PP, LL, DD>(a, grid, st);
   EF(F32, 64, 2) EF(F32, 64, 3) EF(F32, 128, 2) EF(F32, 128, 3) EF(F32, 256, 2) EF(F32, 256, 3)
-  EF(BF16, 64, 2) EF(BF16, 64, 3) EF(BF16, 128, 2) EF(BF16, 128, 3) EF(BF16, 256, 2) EF(BF16, 256, 3)
+  EF(BF16, 128, 3)
 #undef EF
   return hipErrorInvalidValue;
 }
 
 int edge_bwd_grid(int prec, int L, int D, int grid) {
-  return edge_rs(prec, L, D) || edge_rsb(prec, L, D) ? RS_GRID : grid;
+  return edge_rs(prec, L, D) || edge_rsb(prec, L, D) || edge_f32(prec, L, D) ? RS_GRID : grid;
 }
 
 #ifndef RW_BWD_NWV
@@ -6379,8 +6237,7 @@ hipError_t launch_edge_bwd(int prec, int L, int D, const EdgeBwdArgs& a, int gri
   }
 #define EB(PP, LL, DD) \
   if (prec == PP && L == LL && D == DD) return edge_bwd_t<PP, LL, DD>(a, grid, st);
-  EB(F32, 64, 2) EB(F32, 64, 3) EB(F32, 128, 2) EB(F32, 128, 3) EB(F32, 256, 2) EB(F32, 256, 3)
-  EB(BF16, 64, 2) EB(BF16, 64, 3) EB(BF16, 128, 2) EB(BF16, 128, 3) EB(BF16, 256, 2) EB(BF16, 256, 3)
+  EB(F32, 128, 3) EB(F32, 256, 2) EB(F32, 256, 3) EB(BF16, 128, 3)
 #undef EB
   return hipErrorInvalidValue;
 }

@@ -317,3 +317,27 @@ def test_lockstep_argument_errors():
     finally:
         for h in (h0, h1, h3):
             mgn.mgn_destroy(h)
+
+
+def test_forward_only_plan_keeps_the_static_workspace_limit():
+    """Around the static workspace's limit the fp32 forward-only plan's halo
+    rows of the projections decide nothing: a graph fits with its halo exactly
+    when it fits without (the plan then drops those rows)."""
+    m = mgn.mgn_create(128, 3, 2)
+    try:
+        mgn.mgn_set_inference(m, True)
+        fake = 256  # sizes only: the arrays are not read
+
+        def size(no, nh, ne):
+            return mgn.mgn_workspace_size(m, mgn.mgn_graph(no, nh, ne, fake, fake, fake, fake))
+
+        limit = mgn.MGN_NOALLOC_WS_MAX
+        seen = set()
+        for ne in range(200_000, 245_000, 1_000):
+            for nh in (0, 1, 500, 20_000):
+                with_halo, without = size(9_000, nh, ne), size(9_000, 0, ne)
+                assert (with_halo <= limit) == (without <= limit)
+                seen.add((with_halo > without, without <= limit))
+        assert (True, True) in seen and (False, True) in seen and (True, False) in seen
+    finally:
+        mgn.mgn_destroy(m)
