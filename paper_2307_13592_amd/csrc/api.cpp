@@ -19,7 +19,7 @@ namespace {
 
 thread_local std::string g_err;  // last error of calls without a model
 
-constexpr int BWD_GRID = 1024;   // fixed persistent grid of the backward kernels (multiple of 8)
+constexpr int BWD_GRID = 512;    // largest persistent grid of the backward kernels (multiple of 8)
 constexpr int FWD_EDGE_GRID = 2048;
 
 struct LinL {
@@ -38,7 +38,7 @@ struct MlpL {
 
 struct WsPlan {
   size_t erecv, chunk, unit_r, nunits, V, V16, PROJ, AGG, ES, DV[2], DAGG, DZS, DE, DEL_E[3], HID_E[2], DEL_N[3], HID_N[2],
-      HID_NK, HID_E1, PART, VPART, SRANGE, PSH, total;
+      HID_NK, HID_E1, PART, VPART, SRANGE, PSH, vstride, total;
   int64_t max_units;
   // edge-stream checkpointing: interval s (0: every block kept), checkpoints
   bool lean = false;
@@ -319,24 +319,13 @@ WsPlan make_plan(const mgn_model* m, const mgn_graph* g) {
   // T-form node kernels: every block's first-Linear ReLU output, written by
   // the forward for the backward; checkpointing: one block's, recomputed
   p.HID_NK = rows_keep_h1(m->prec, L, m->D) ? take(2 * (size_t)(p.lean ? 1 : K) * no * L) : 0;
-  // split-K partials: the largest S*O*I over all weight matrices
-  size_t part = 0;
-  const size_t nm = m->mlp.size();
-  for (size_t i = 0; i < nm; ++i) {
-    const MlpL& ml = m->mlp[i];
-    // EncEdge (index 1) and the edge MLPs (even indices 2 .. nm-2) run over edges
-    const bool edge_rows = i == 1 || (i >= 2 && i + 1 < nm && i % 2 == 0);
-    const int64_t R = edge_rows ? ne : nl;
-    for (int j = 0; j < ml.depth; ++j) {
-      const LinL& Ln = ml.lin[j];
-      part = std::max(part, (size_t)dw_splits(R, Ln.out, Ln.in) * Ln.out * Ln.in);
-    }
-  }
-  part = std::max(part, (size_t)dw_stream_parts() * 16384);
-  p.PART = take(4 * part);
+  // weight-gradient partials: of the stream kernels, or of one group's units
+  p.PART = take(4 * std::max((size_t)dw_stream_parts() * 16384, (size_t)DW_MAX_UNITS * 4096));
   int nvec = 0;
   for (const MlpL& ml : m->mlp) nvec = std::max(nvec, ml.nvec);
-  p.VPART = take(4 * (size_t)BWD_GRID * nvec);
+  // bias / LayerNorm partials of a row kernel and of an edge kernel
+  p.vstride = (size_t)BWD_GRID * nvec;
+  p.VPART = take(4 * 2 * p.vstride);
   p.SRANGE = take(8);  // sender-id range of a backward edge chunk
   p.total = o;
   return p;
@@ -653,76 +642,6 @@ hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p,
 
 namespace {
 
-// Weight gradient of Linear j of an MLP: split-K GEMM into the partial
-// buffer, then the fixed-order reduction into d_params.
-// Gradient of Linear L's weight, or of its input columns [col0, col0 + ncols)
-// when ncols >= 0 (the operand a then covers just those columns).
-hipError_t run_dw(mgn_model* m, const LinL& L, DwArgs a, float* d_params, int accumulate, hipStream_t st,
-                  int col0 = 0, int ncols = -1) {
-  a.O = L.out;
-  a.I = ncols < 0 ? L.in : ncols;
-  a.S = dw_splits(a.R, a.O, a.I);
-  a.part = (float*)(m->ws + m->plan.PART);
-  a.L = m->L;
-  float* dst = d_params + L.w + col0;
-  if (a.R == 0) {
-    // no rows: the gradient is zero
-    if (accumulate) return hipSuccess;
-    if (ncols < 0) return launch_zero(dst, (int64_t)L.out * L.in, st);
-    for (int o = 0; o < L.out; ++o) {
-      hipError_t e = launch_zero(dst + (size_t)o * L.in, a.I, st);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  Timed t_(m, MGN_T_WEIGHT_GRAD, st);
-  if (dw_stream_ok(m->prec, a)) return launch_dw_stream(a, dst, L.in, accumulate, st);
-  if (dw_stream_quad_ok(m->prec, a)) return launch_dw_stream_quad(a, dst, L.in, accumulate, st);
-  if (dw_stream_f32_ok(m->prec, a)) return launch_dw_stream_f32(a, dst, L.in, accumulate, st);
-  if ((a.O > 128 || a.I > 128) && a.O % 128 == 0 && a.I % 128 == 0) {
-    // wider layers (l = 256) as 128 x 128 blocks on the register-resident
-    // kernels: each block re-reads its column ranges of both operands
-    DwArgs q = a;
-    q.O = 128;
-    q.I = 128;
-    const bool bf = dw_stream_ok(m->prec, q), f32 = dw_stream_f32_ok(m->prec, q);
-    if (bf || f32) {
-      const size_t st_sz = tsize(m);
-      const size_t ds = a.d_kind == 1 ? 4 : st_sz, as = a.a_kind == 1 ? 4 : st_sz;
-      for (int o0 = 0; o0 < a.O; o0 += 128)
-        for (int i0 = 0; i0 < a.I; i0 += 128) {
-          q.delta = (const char*)a.delta + ds * o0;
-          q.a0 = (const char*)a.a0 + as * i0;
-          float* qd = dst + (size_t)o0 * L.in + i0;
-          hipError_t e = bf ? launch_dw_stream(q, qd, L.in, accumulate, st)
-                            : launch_dw_stream_f32(q, qd, L.in, accumulate, st);
-          if (e != hipSuccess) return e;
-        }
-      return hipSuccess;
-    }
-  }
-  hipError_t e = launch_dw(m->prec, a, st);
-  if (e == hipSuccess) e = launch_dw_reduce(a.part, a.S, a.O, a.I, dst, L.in, accumulate, st);
-  return e;
-}
-
-hipError_t run_vec(mgn_model* m, const MlpL& ml, float* d_params, int accumulate, hipStream_t st,
-                   int slots = BWD_GRID) {
-  VecSeg segs[4];
-  int n = 0, off = 0;
-  for (int j = 0; j < ml.depth; ++j) {
-    segs[n++] = VecSeg{off, ml.lin[j].b, ml.lin[j].out};
-    off += (j + 1 < ml.depth) ? m->L : ml.lin[j].out;
-  }
-  if (ml.gamma >= 0) segs[n++] = VecSeg{off, ml.gamma, 2 * ml.lin[ml.depth - 1].out};
-  Timed t_(m, MGN_T_WEIGHT_GRAD, st);
-  return launch_vec_reduce((float*)(m->ws + m->plan.VPART), slots, ml.nvec, segs, n, d_params, accumulate, st);
-}
-
-}  // namespace
-
-namespace {
-
 // Views of the buffers of the model's current step (the plan, workspace and
 // graph recorded by the forward's first stage).
 struct Views {
@@ -905,7 +824,7 @@ struct Bwd {
   size_t ts;
   float* DV[2];
   void* DE;  // dL/de in the storage type
-  float *DAGG, *DZS, *VP;
+  float *DAGG, *DZS, *VP, *VPE;  // VP, VPE: vector partials of the row and of the edge kernels
   int32_t* erecv;
   void *DEL_N[3], *HID_N[2], *DEL_E[3], *HID_E[2];
   float* d_params;
@@ -921,6 +840,7 @@ struct Bwd {
     DAGG = (float*)(ws + p.DAGG);
     DZS = (float*)(ws + p.DZS);
     VP = (float*)(ws + p.VPART);
+    VPE = VP + p.vstride;
     erecv = (int32_t*)(ws + p.erecv);
     for (int j = 0; j < 3; ++j) DEL_N[j] = ws + p.DEL_N[j];
     for (int j = 0; j < 2; ++j) HID_N[j] = ws + p.HID_N[j];
@@ -941,6 +861,98 @@ struct Bwd {
     return a;
   }
 
+  // Weight and vector gradients waiting for one launch (flush): their operands
+  // must stay as they are until then.
+  DwGroup grp{};
+
+  // Weight gradient of Linear L, or of its input columns [col0, col0 + ncols)
+  // when ncols >= 0 (the operand a then covers just those columns).  Layers of
+  // 128 or 256 columns over many rows run at once on the stream kernels
+  // (memory-bound there: a wave's 128 x 128 tile reads each operand once);
+  // the rest joins the group.
+  hipError_t run_dw(const LinL& Ln, DwArgs a, int acc, int col0 = 0, int ncols = -1) {
+    a.O = Ln.out;
+    a.I = ncols < 0 ? Ln.in : ncols;
+    a.part = (float*)(ws + p.PART);
+    float* dst = d_params + Ln.w + col0;
+    const bool tile = dw_stream_ok(m->prec, a);
+    if (tile || dw_stream_quad_ok(m->prec, a)) {
+      Timed t_(m, MGN_T_WEIGHT_GRAD, st);
+      return tile ? launch_dw_stream(a, dst, Ln.in, acc, st) : launch_dw_stream_quad(a, dst, Ln.in, acc, st);
+    }
+    if (a.O % 128 == 0 && a.I % 128 == 0) {
+      // fp32, wider layers as 128 x 128 blocks
+      DwArgs b = a;
+      b.O = b.I = 128;
+      if (dw_stream_f32_ok(m->prec, b)) {
+        Timed t_(m, MGN_T_WEIGHT_GRAD, st);
+        for (int o0 = 0; o0 < a.O; o0 += 128)
+          for (int i0 = 0; i0 < a.I; i0 += 128) {
+            b.delta = (const float*)a.delta + o0;
+            b.a0 = (const float*)a.a0 + i0;
+            const hipError_t e = launch_dw_stream_f32(b, dst + (size_t)o0 * Ln.in + i0, Ln.in, acc, st);
+            if (e != hipSuccess) return e;
+          }
+        return hipSuccess;
+      }
+    }
+    if (grp.n == DW_JOBS) {
+      hipError_t e = flush();
+      if (e != hipSuccess) return e;
+    }
+    DwJob& j = grp.job[grp.n++];
+    j = DwJob{};
+    j.D = a.delta;
+    j.A = a.a0;
+    j.A2 = a.a2;
+    j.n_first = a.a_kind == 4 ? a.n_owned : a.R;
+    j.R = a.R;
+    j.dst = dst;
+    j.ldd = a.ldd;
+    j.lda = a.lda0;
+    j.O = a.O;
+    j.I = a.I;
+    j.ldw = Ln.in;
+    j.accumulate = acc;
+    j.d32 = m->prec == F32 || a.d_kind == 1;
+    j.a32 = m->prec == F32 || a.a_kind != 0;
+    j.avec = aligned(a.a0, 16) && aligned(a.a2, 16) && a.lda0 % 4 == 0 && a.I % 4 == 0;
+    j.ti = (a.I + 63) / 64;
+    j.tiles = (a.O + 63) / 64 * j.ti;
+    return hipSuccess;
+  }
+
+  // Bias and LayerNorm gradients of an MLP from the partials of `slots` workgroups.
+  hipError_t run_vec(const MlpL& ml, const float* part, int acc, int slots) {
+    if (grp.nv == DW_VECS) {
+      hipError_t e = flush();
+      if (e != hipSuccess) return e;
+    }
+    DwVec& v = grp.vec[grp.nv++];
+    v = DwVec{};
+    v.part = part;
+    v.dst = d_params;
+    v.slots = slots;
+    v.nvec = ml.nvec;
+    v.accumulate = acc;
+    int off = 0;
+    for (int j = 0; j < ml.depth; ++j) {
+      v.seg[v.nseg++] = VecSeg{off, ml.lin[j].b, ml.lin[j].out};
+      off += (j + 1 < ml.depth) ? L : ml.lin[j].out;
+    }
+    if (ml.gamma >= 0) v.seg[v.nseg++] = VecSeg{off, ml.gamma, 2 * ml.lin[ml.depth - 1].out};
+    return hipSuccess;
+  }
+
+  hipError_t flush() {
+    if (grp.n + grp.nv == 0) return hipSuccess;
+    grp.part = (float*)(ws + p.PART);
+    Timed t_(m, MGN_T_WEIGHT_GRAD, st);
+    const hipError_t e = launch_dw_group(m->prec, grp, st);
+    grp.n = grp.nv = 0;
+    return e;
+  }
+
   // weight gradients of the hidden / last Linears from the stored activations
   hipError_t dw_hidden(const MlpL& ml, int64_t R, void* const* del, void* const* hid, int ld_last, int acc) {
     for (int j = 1; j < D; ++j) {
@@ -951,7 +963,7 @@ struct Bwd {
       a.a0 = hid[j - 1];
       a.lda0 = L;
       a.R = R;
-      hipError_t r = run_dw(m, ml.lin[j], a, d_params, acc, st);
+      hipError_t r = run_dw(ml.lin[j], a, acc);
       if (r != hipSuccess) return r;
     }
     return hipSuccess;
@@ -968,10 +980,10 @@ struct Bwd {
     a.fout = m->cfg.node_out;
     {
       Timed t_(m, MGN_T_NODE_BWD, st);
-      e = launch_rows_bwd(m->prec, L, D, DECODER, a, BWD_GRID, st);
+      e = launch_rows_bwd(m->prec, L, D, DECODER, a, rows_bwd_grid(m->prec, L, D, DECODER, no, BWD_GRID), st);
     }
     CHK("decoder");
-    e = run_vec(m, ml, d_params, accumulate, st);
+    e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, DECODER, no, BWD_GRID));
     CHK("decoder vec");
     DwArgs w{};
     w.delta = DEL_N[0];
@@ -980,10 +992,12 @@ struct Bwd {
     w.a0 = b.V(K);
     w.lda0 = L;
     w.R = no;
-    e = run_dw(m, ml.lin[0], w, d_params, accumulate, st);
+    e = run_dw(ml.lin[0], w, accumulate);
     CHK("decoder dW");
     e = dw_hidden(ml, no, DEL_N, HID_N, 16, accumulate);
     CHK("decoder dW");
+    e = flush();
+    CHK("decoder gradients");
     return MGN_OK;
   }
 
@@ -1047,10 +1061,10 @@ struct Bwd {
       a.dx1 = DAGG;
       {
         Timed t_(m, MGN_T_NODE_BWD, st);
-        e = launch_rows_bwd(m->prec, L, D, NODE_BLOCK, a, BWD_GRID, st);
+        e = launch_rows_bwd(m->prec, L, D, NODE_BLOCK, a, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, no, BWD_GRID), st);
       }
       CHK("node block");
-      e = run_vec(m, ml, d_params, accumulate, st, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, BWD_GRID));
+      e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, no, BWD_GRID));
       CHK("node vec");
       // first Linear, input [v | agg]: one weight gradient per column block
       // (each a plain row-major operand, so the register-resident kernels
@@ -1063,11 +1077,11 @@ struct Bwd {
       const bool st_v = m->prec == F32 || !p.lean;  // v in the storage type (fp32 V) or bf16 copy
       w.a_kind = (m->prec == BF16 && !p.lean) ? 1 : 0;
       w.a0 = st_v ? (const void*)b.V(k) : b.V16(k);
-      e = run_dw(m, ml.lin[0], w, d_params, accumulate, st, 0, L);
+      e = run_dw(ml.lin[0], w, accumulate, 0, L);
       CHK("node dW (v block)");
       w.a_kind = m->prec == BF16 ? 1 : 0;
       w.a0 = b.AGG(k);
-      e = run_dw(m, ml.lin[0], w, d_params, accumulate, st, L, L);
+      e = run_dw(ml.lin[0], w, accumulate, L, L);
       CHK("node dW (agg block)");
       e = dw_hidden(ml, no, DEL_N, hidk, L, accumulate);
       CHK("node dW");
@@ -1102,7 +1116,7 @@ struct Bwd {
       a.hid_in = h1;
       for (int j = 0; j < 3; ++j) a.delta[j] = DEL_E[j];
       for (int j = 0; j < 2; ++j) a.hid[j] = HID_E[j];
-      a.vpart = VP;
+      a.vpart = VPE;
       a.nvec = ml.nvec;
       a.eps = m->cfg.ln_eps;
       for (size_t c = 0; c < nch; ++c) {
@@ -1117,7 +1131,7 @@ struct Bwd {
           e = p.f32 ? launch_edge_bwd_f32(L, D, a, rows, st) : launch_edge_bwd(m->prec, L, D, a, BWD_GRID, st);
         }
         CHK("edge block");
-        e = run_vec(m, ml, d_params, acc, st, edge_bwd_grid(m->prec, L, D, BWD_GRID));
+        e = run_vec(ml, VPE, acc, edge_bwd_grid(m->prec, L, D, BWD_GRID));
         CHK("edge vec");
         void* hid_c[2] = {h1 ? (void*)((char*)h1 + ts * (size_t)e0 * L) : HID_E[0], HID_E[1]};
         e = dw_hidden(ml, rows, DEL_E, hid_c, L, acc);
@@ -1130,9 +1144,12 @@ struct Bwd {
         w.a0 = (const char*)b.ES(k) + ts * (size_t)e0 * L;
         w.lda0 = L;
         w.R = rows;
-        e = run_dw(m, ml.lin[0], w, d_params, acc, st, 0, L);
+        e = run_dw(ml.lin[0], w, acc, 0, L);
         CHK("edge dW (e block)");
         if (nch > 1) {
+          // the next chunk's backward reuses the buffers
+          e = flush();
+          CHK("edge gradients");
           // per-sender sums of dz_0, chunk by chunk in ascending edge order:
           // zero once, then each chunk adds to the senders of its edges only
           Timed t_(m, MGN_T_INPUT_GRAD, st);
@@ -1181,9 +1198,11 @@ struct Bwd {
           wn.a2 = Hk;
           wn.n_owned = no;
         }
-        e = run_dw(m, ml.lin[0], wn, d_params, accumulate, st, (1 + side) * L, L);
+        e = run_dw(ml.lin[0], wn, accumulate, (1 + side) * L, L);
         CHK("edge dW (node blocks)");
       }
+      e = flush();
+      CHK("block gradients");
     }
     return MGN_OK;
   }
@@ -1199,10 +1218,10 @@ struct Bwd {
       a.dm = DV[a_];
       {
         Timed t_(m, MGN_T_NODE_BWD, st);
-        e = launch_rows_bwd(m->prec, L, D, ENC_NODE, a, BWD_GRID, st);
+        e = launch_rows_bwd(m->prec, L, D, ENC_NODE, a, rows_bwd_grid(m->prec, L, D, ENC_NODE, no, BWD_GRID), st);
       }
       CHK("EncNode");
-      e = run_vec(m, ml, d_params, accumulate, st, rows_bwd_grid(m->prec, L, D, ENC_NODE, BWD_GRID));
+      e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, ENC_NODE, no, BWD_GRID));
       CHK("EncNode vec");
       DwArgs w{};
       w.delta = DEL_N[0];
@@ -1211,7 +1230,7 @@ struct Bwd {
       w.a0 = m->nf;
       w.lda0 = m->cfg.node_in;
       w.R = no;
-      e = run_dw(m, ml.lin[0], w, d_params, accumulate, st);
+      e = run_dw(ml.lin[0], w, accumulate);
       CHK("EncNode dW");
       e = dw_hidden(ml, no, DEL_N, HID_N, L, accumulate);
       CHK("EncNode dW");
@@ -1223,6 +1242,7 @@ struct Bwd {
         const int acc = accumulate || c > 0;
         const int64_t e0 = p.ce[c], rows = p.ce[c + 1] - p.ce[c];
         RowsBwdArgs a = rows_args(ml, rows, DEL_E, HID_E);
+        a.vpart = VPE;
         a.in0 = m->ef + (size_t)e0 * m->cfg.edge_in;
         a.fin = m->cfg.edge_in;
         // dL/de^0 (block 0 wrote it in plain column order, in the storage type)
@@ -1234,10 +1254,10 @@ struct Bwd {
         if (w1s) a.w1_part = (float*)(ws + p.PART);
         {
           Timed t_(m, MGN_T_NODE_BWD, st);
-          e = launch_rows_bwd(m->prec, L, D, ENC_EDGE, a, BWD_GRID, st);
+          e = launch_rows_bwd(m->prec, L, D, ENC_EDGE, a, rows_bwd_grid(m->prec, L, D, ENC_EDGE, rows, BWD_GRID), st);
         }
         CHK("EncEdge");
-        e = run_vec(m, ml, d_params, acc, st, rows_bwd_grid(m->prec, L, D, ENC_EDGE, BWD_GRID));
+        e = run_vec(ml, VPE, acc, rows_bwd_grid(m->prec, L, D, ENC_EDGE, rows, BWD_GRID));
         CHK("EncEdge vec");
         if (w1s) {
           Timed t_(m, MGN_T_WEIGHT_GRAD, st);
@@ -1250,11 +1270,13 @@ struct Bwd {
           w.a0 = a.in0;
           w.lda0 = m->cfg.edge_in;
           w.R = rows;
-          e = run_dw(m, ml.lin[0], w, d_params, acc, st);
+          e = run_dw(ml.lin[0], w, acc);
         }
         CHK("EncEdge dW");
         e = dw_hidden(ml, rows, DEL_E, HID_E, L, acc);
         CHK("EncEdge dW");
+        e = flush();  // (with the node encoder's; the next chunk reuses the buffers)
+        CHK("encoder gradients");
       }
     } else if (!accumulate) {
       // no edges reach the output: the edge encoder's gradient is zero
@@ -1263,6 +1285,8 @@ struct Bwd {
       e = launch_zero(d_params + b0, end - b0, st);
       CHK("EncEdge zero");
     }
+    e = flush();
+    CHK("encoder gradients");
     return MGN_OK;
   }
 };

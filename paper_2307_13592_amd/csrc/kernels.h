@@ -110,32 +110,55 @@ struct InGradArgs {
   int64_t n_local, n_owned;
 };
 
+// Operands of a weight gradient dW[o][i] = sum over rows of delta[row][o] *
+// A[row][i].
 struct DwArgs {
   const void* delta;  // d_kind 0: storage type [R][ldd]; 1: fp32 [R][ldd]
   int d_kind;
   int ldd;
   int O, I;
-  int a_kind;         // 0 dense storage type, 1 dense fp32, 2 edge concat, 3 node concat,
-                      // 4 node rows fp32 (owned rows a0, halo rows a2; row stride lda0),
-                      // 5 node concat with the v part in bf16 (a3) and agg fp32 (a1)
-  const void* a0;     // dense source / e^k / v
+  int a_kind;         // 0 dense storage type, 1 dense fp32, 4 node rows fp32 (owned rows a0, halo rows a2)
+  const void* a0;
   int lda0;
-  const float* a1;    // node concat: agg; edge concat: V (owned)
-  const float* a2;    // edge concat: H (halo)
-  const void* a3;     // edge concat, bf16 mode: bf16 copy of the node rows (owned then halo), or null
-  const int32_t* send;
-  const int32_t* erecv;
+  const float* a2;
   int64_t n_owned;
-  int L;
   int64_t R;
-  int S;
-  float* part;        // [S][O][I]
+  float* part;        // partials (stream kernels)
 };
 
 struct VecSeg {
   int vec_off;
   int64_t param_off;
   int len;
+};
+
+// One weight gradient of a group launch (dw.hip): dst[o * ldw + i] (+)= sum
+// over the rows r < R of D[r][o] * A[r][i].  D: ldd columns (a multiple of 4,
+// those past O readable), storage type or (d32) fp32; A: storage type or (a32)
+// fp32, rows from n_first on taken from A2.
+struct DwJob {
+  const void *D, *A, *A2;
+  int64_t n_first, R;
+  float* dst;
+  int ldd, lda, O, I, ldw;
+  int accumulate, d32, a32;
+  int avec;                    // A rows are aligned for 4-column loads
+  int ti, tiles, S, unit0;     // 64 x 64 tiles (ti per row of tiles); set by launch_dw_group: row splits, first unit
+};
+// Bias / LayerNorm gradients: sums over `slots` rows of part [slots][nvec].
+struct DwVec {
+  const float* part;
+  float* dst;
+  int slots, nvec, nseg, accumulate;
+  VecSeg seg[4];
+};
+constexpr int DW_JOBS = 16, DW_VECS = 4;
+constexpr int DW_MAX_UNITS = 4096;  // of 4096 floats of partials each
+struct DwGroup {
+  DwJob job[DW_JOBS];
+  DwVec vec[DW_VECS];
+  int n, nv, units;
+  float* part;
 };
 
 // ------------------------------------------------------------ launchers ---
@@ -182,8 +205,9 @@ bool rows_keep_h1(int prec, int L, int D);
 hipError_t launch_rows_fwd(int prec, int L, int D, int kind, const RowsFwdArgs& a, hipStream_t st);
 hipError_t launch_edge_fwd(int prec, int L, int D, const EdgeFwdArgs& a, int grid, hipStream_t st);
 hipError_t launch_rows_bwd(int prec, int L, int D, int kind, const RowsBwdArgs& a, int grid, hipStream_t st);
-// Workgroups (= vector-partial slots) launch_rows_bwd uses when asked for `grid`.
-int rows_bwd_grid(int prec, int L, int D, int kind, int grid);
+// Workgroups (= vector-partial slots) launch_rows_bwd uses for `rows` rows when
+// asked for at most `grid`.
+int rows_bwd_grid(int prec, int L, int D, int kind, int64_t rows, int grid);
 // Number of per-wave partials (RowsBwdArgs::w1_part) with which the backward
 // of `kind` forms its first Linear's weight gradient itself, or 0 if it
 // stores delta[0] for a separate weight-gradient GEMM instead.
@@ -229,11 +253,10 @@ hipError_t launch_dw_stream_quad(const DwArgs& a, float* dst, int ldw, int accum
 // wave partials in plain [o][i] order, then the fixed-order split reduction.
 bool dw_stream_f32_ok(int prec, const DwArgs& a);
 hipError_t launch_dw_stream_f32(const DwArgs& a, float* dst, int ldw, int accumulate, hipStream_t st);
-hipError_t launch_dw(int prec, const DwArgs& a, hipStream_t st);
+// All jobs and vectors of g (two launches); g's split fields are set here.
+hipError_t launch_dw_group(int prec, DwGroup& g, hipStream_t st);
 hipError_t launch_dw_reduce(const float* part, int S, int O, int I, float* dst, int ldw, int accumulate,
                             hipStream_t st);
-hipError_t launch_vec_reduce(const float* vpart, int nwg, int nvec, const VecSeg* segs, int nseg, float* dparams,
-                             int accumulate, hipStream_t st);
 // Masked MSE and its gradient; the mean is over global_rows rows when > 0,
 // else over this call's masked rows.
 hipError_t launch_mse(const float* out, const float* target, const uint8_t* mask, int64_t n, int d,
@@ -241,6 +264,5 @@ hipError_t launch_mse(const float* out, const float* target, const uint8_t* mask
 
 // tile sizes the host needs to know (rows per edge sub-tile, per prec/L/D)
 int edge_tile_rows(int prec, int L, int D);
-int dw_splits(int64_t R, int O, int I);
 
 }  // namespace mgn

@@ -5219,207 +5219,6 @@ __global__ __launch_bounds__(NT) void sender_range_kernel(const int32_t* __restr
   }
 }
 
-// -------------------------------------------------- weight gradients ---
-// part[s][o][i] = sum over rows of split s of delta[row][o] * A[row][i], as an
-// MFMA GEMM with both operands staged transposed in LDS (rows contiguous).
-constexpr int DW_TO = 128, DW_TI = 128, DW_RC = 64;
-
-// EL consecutive elements (16 bytes of storage type) of row `row` of the
-// weight-gradient input operand, starting at column col, as storage type.
-template <class P>
-__device__ __forceinline__ uint4 dw_load_a(const DwArgs& a, int64_t row, int col) {
-  using T = typename P::T;
-  T v[P::EL];
-  if (a.a_kind == 0) {
-    return *reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.a0) + row * a.lda0 + col);
-  } else if (a.a_kind == 1) {
-    const float* src = reinterpret_cast<const float*>(a.a0) + row * a.lda0 + col;
-#pragma unroll
-    for (int e = 0; e < P::EL; ++e) v[e] = P::cvt((col + e < a.lda0) ? src[e] : 0.f);
-  } else if (a.a_kind == 2) {
-    const int L = a.L;
-    if (col < L) return *reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.a0) + row * L + col);
-    const int64_t node = col < 2 * L ? (int64_t)a.send[row] : (int64_t)a.erecv[row];
-    const int c = col < 2 * L ? col - L : col - 2 * L;
-    if (a.a3) {  // bf16 copy of the node rows, owned then halo
-      return *reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.a3) + node * L + c);
-    }
-    const float* src = node < a.n_owned ? a.a1 + node * L + c : a.a2 + (node - a.n_owned) * L + c;
-#pragma unroll
-    for (int e = 0; e < P::EL; ++e) v[e] = P::cvt(src[e]);
-  } else if (a.a_kind == 3) {
-    const int L = a.L;
-    const float* src = (col < L ? reinterpret_cast<const float*>(a.a0) + row * L + col : a.a1 + row * L + (col - L));
-#pragma unroll
-    for (int e = 0; e < P::EL; ++e) v[e] = P::cvt(src[e]);
-  } else if (a.a_kind == 5) {
-    // node concat with v as bf16 rows (bf16 mode; EL = 8 columns never straddle v | agg)
-    const int L = a.L;
-    if (col < L) return *reinterpret_cast<const uint4*>(reinterpret_cast<const T*>(a.a3) + row * L + col);
-    const float* src = a.a1 + row * L + (col - L);
-#pragma unroll
-    for (int e = 0; e < P::EL; ++e) v[e] = P::cvt(src[e]);
-  } else {
-    // node rows, fp32: owned rows from a0, halo rows from a2
-    const float* src = row < a.n_owned ? reinterpret_cast<const float*>(a.a0) + row * a.lda0 + col
-                                       : a.a2 + (row - a.n_owned) * a.lda0 + col;
-#pragma unroll
-    for (int e = 0; e < P::EL; ++e) v[e] = P::cvt(src[e]);
-  }
-  return *reinterpret_cast<const uint4*>(v);
-}
-
-// Transposed LDS tiles [column][row] of DW_RC rows.  A wave stores 16 rows
-// of four column groups (EL columns each) at once.  In fp32 the row padding
-// alone spreads them over the banks; in bf16 the four groups' columns are
-// 8 apart, which the padding maps onto the same banks, so the row index is
-// XORed with 16 * ((column / 8) % 4).  Aligned 16-element runs stay
-// contiguous, so MFMA fragments (EL consecutive rows) remain 16-byte reads.
-template <class P>
-__device__ __forceinline__ int dw_swz(int col, int r) {
-  if constexpr (P::EL == 4) return r;
-  else return r ^ (16 * ((col >> 3) & 3));
-}
-
-// SPLIT (bf16 only): delta is fp32 and enters the products as hi + lo, two
-// bf16 operands whose sum is within 2^-17 of it (relative).
-template <int P_, bool SPLIT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void dw_kernel(DwArgs a) {
-  using P = typename PrecOf<P_>::type;
-  using T = typename P::T;
-  static_assert(!SPLIT || sizeof(T) == 2, "split operands are a bf16-mode form");
-  constexpr int LDT = DW_RC + P::PAD;
-  constexpr int GPR = DW_TO / P::EL;              // 16-byte groups per operand row
-  constexpr int IT = DW_RC * GPR / NT;            // loads per thread per operand per chunk
-  __shared__ __align__(16) T Dt[DW_TO * LDT];
-  __shared__ __align__(16) T Dl[SPLIT ? DW_TO * LDT : 16];
-  __shared__ __align__(16) T At[DW_TI * LDT];
-  const int ot = blockIdx.x, itl = blockIdx.y, s = blockIdx.z;
-  const int o0 = ot * DW_TO, i0 = itl * DW_TI;
-  const int64_t per = (a.R + a.S - 1) / a.S;
-  const int64_t rb = (int64_t)s * per, re = rb + per < a.R ? rb + per : a.R;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wo = (wave >> 1) * 64, wi = (wave & 1) * 64;  // this wave's 64x64 quadrant
-  floatx4 acc[4][4];
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int n = 0; n < 4; ++n) acc[m][n] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const T* dl = reinterpret_cast<const T*>(a.delta);
-  // thread -> (row, column group): 16 consecutive rows per 16 lanes, four
-  // column groups per wave (64 contiguous bytes of each row per wave)
-  auto rowof = [&](int j) { const int idx = threadIdx.x + j * NT; return (idx & 15) + 16 * (idx / (16 * GPR)); };
-  auto grpof = [&](int j) { const int idx = threadIdx.x + j * NT; return ((idx >> 4) % GPR) * P::EL; };
-  uint4 rd[IT], ra[IT], rl[SPLIT ? IT : 1];
-  auto load = [&](int64_t c0) {
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int r = rowof(j), g = grpof(j);
-      const int64_t row = c0 + r;
-      rd[j] = make_uint4(0, 0, 0, 0);
-      ra[j] = make_uint4(0, 0, 0, 0);
-      if constexpr (SPLIT) rl[j] = make_uint4(0, 0, 0, 0);
-      if (row < re) {
-        if constexpr (SPLIT) {
-          // fp32 delta (a.O and a.ldd multiples of 8): 8 values, hi and lo halves
-          if (o0 + g < a.O) {
-            const float* src = reinterpret_cast<const float*>(a.delta) + row * a.ldd + o0 + g;
-            const float4 x0 = reinterpret_cast<const float4*>(src)[0], x1 = reinterpret_cast<const float4*>(src)[1];
-            const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-            uint16_t h[8], l[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              h[e] = f2bf(x[e]);
-              l[e] = f2bf(x[e] - bf2f(h[e]));
-            }
-            rd[j] = *reinterpret_cast<const uint4*>(h);
-            rl[j] = *reinterpret_cast<const uint4*>(l);
-          }
-        } else if (o0 + g < a.O) {
-          if (o0 + g + P::EL <= a.ldd && (a.ldd % P::EL) == 0) {
-            rd[j] = *reinterpret_cast<const uint4*>(dl + row * a.ldd + o0 + g);
-          } else {
-            T v[P::EL];
-#pragma unroll
-            for (int e = 0; e < P::EL; ++e) v[e] = (o0 + g + e < a.O) ? dl[row * a.ldd + o0 + g + e] : P::cvt(0.f);
-            rd[j] = *reinterpret_cast<const uint4*>(v);
-          }
-        }
-        if (i0 + g < a.I) ra[j] = dw_load_a<P>(a, row, i0 + g);
-      }
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int j = 0; j < IT; ++j) {
-      const int r = rowof(j), g = grpof(j);
-      const T* vd = reinterpret_cast<const T*>(&rd[j]);
-      const T* va = reinterpret_cast<const T*>(&ra[j]);
-#pragma unroll
-      for (int e = 0; e < P::EL; ++e) {
-        const int c = g + e;
-        Dt[c * LDT + dw_swz<P>(c, r)] = (o0 + c < a.O) ? vd[e] : P::cvt(0.f);
-        At[c * LDT + dw_swz<P>(c, r)] = (i0 + c < a.I) ? va[e] : P::cvt(0.f);
-      }
-      if constexpr (SPLIT) {
-        const T* vl = reinterpret_cast<const T*>(&rl[j]);
-#pragma unroll
-        for (int e = 0; e < P::EL; ++e) {
-          const int c = g + e;
-          Dl[c * LDT + dw_swz<P>(c, r)] = (o0 + c < a.O) ? vl[e] : P::cvt(0.f);
-        }
-      }
-    }
-  };
-  if (rb < re) load(rb);
-  for (int64_t c0 = rb; c0 < re; c0 += DW_RC) {
-    store();
-    __syncthreads();
-    if (c0 + DW_RC < re) load(c0 + DW_RC);  // next chunk in flight during the products
-#pragma unroll
-    for (int kg = 0; kg < DW_RC / P::KG; ++kg) {
-      uint4 af[4], bf[4];
-      const int kk = kg * P::KG + (lane >> 4) * P::EL;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int c = wo + m * 16 + (lane & 15);
-        af[m] = *reinterpret_cast<const uint4*>(Dt + c * LDT + dw_swz<P>(c, kk));
-      }
-#pragma unroll
-      for (int n = 0; n < 4; ++n) {
-        const int c = wi + n * 16 + (lane & 15);
-        bf[n] = *reinterpret_cast<const uint4*>(At + c * LDT + dw_swz<P>(c, kk));
-      }
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < 4; ++n) P::mma(acc[m][n], af[m], bf[n]);
-      if constexpr (SPLIT) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const int c = wo + m * 16 + (lane & 15);
-          af[m] = *reinterpret_cast<const uint4*>(Dl + c * LDT + dw_swz<P>(c, kk));
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-#pragma unroll
-          for (int n = 0; n < 4; ++n) P::mma(acc[m][n], af[m], bf[n]);
-      }
-    }
-    __syncthreads();
-  }
-  float* dst = a.part + (int64_t)s * a.O * a.I;
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
-#pragma unroll
-    for (int n = 0; n < 4; ++n)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int o = o0 + wo + m * 16 + acc_row(r), i = i0 + wi + n * 16 + acc_col();
-        if (o < a.O && i < a.I) dst[(int64_t)o * a.I + i] = acc[m][n][r];
-      }
-}
-
 // ------------------------------------- weight gradients, register-resident ---
 // dW = D^T A for bf16 row-major D [R][ldd] and A [R][lda], 128 columns each
 // (the per-edge layers of the row-split path at l = 128), without LDS or
@@ -5716,35 +5515,6 @@ __global__ __launch_bounds__(NT) void dw_reduce_kernel(const float* __restrict__
     float* d = dst + (i / I) * ldw + (i % I);
     const float s = accumulate ? *d : 0.f;
     *d = s + t4;
-  }
-}
-
-struct VecSegs {
-  VecSeg s[4];
-  int n;
-};
-
-// The same four-way split of the slot sums as dw_reduce_kernel.
-__global__ __launch_bounds__(NT) void vec_reduce_kernel(const float* __restrict__ vpart, int nwg, int nvec,
-                                                        VecSegs segs, float* __restrict__ dparams, int accumulate) {
-  __shared__ float sh[NT];
-  const int j = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + j;
-  float t = 0.f;
-  if (i < nvec) {
-#pragma unroll 8
-    for (int w = q; w < nwg; w += 4) t += vpart[(int64_t)w * nvec + i];
-  }
-  sh[threadIdx.x] = t;
-  __syncthreads();
-  if (q != 0 || i >= nvec) return;
-  t = ((sh[j] + sh[64 + j]) + sh[128 + j]) + sh[192 + j];
-  for (int k = 0; k < segs.n; ++k) {
-    const VecSeg& sg = segs.s[k];
-    if (i >= sg.vec_off && i < sg.vec_off + sg.len) {
-      float* d = dparams + sg.param_off + (i - sg.vec_off);
-      *d = (accumulate ? *d : 0.f) + t;
-    }
   }
 }
 
@@ -6081,9 +5851,26 @@ static bool rows_rt_bwd(int prec, int L, int D, int kind, bool hid_in) {
   return rows_rt(prec, L, D, kind) && (kind == ENC_EDGE || kind == ENC_NODE || (kind == NODE_BLOCK && hid_in));
 }
 
-int rows_bwd_grid(int prec, int L, int D, int kind, int grid) {
-  return rows_rs(prec, L, D, kind) || rows_rt_bwd(prec, L, D, kind, false) || rows_rw(prec, L, D, kind) ? RS_GRID
-                                                                                                       : grid;
+// Rows per tile of rows_bwd_kernel.
+template <int P_, int L, int D>
+static int rows_bwd_tile(int kind) {
+  using P = typename PrecOf<P_>::type;
+  return kind == ENC_NODE     ? RowTM<P, ENC_NODE, L, D>::value
+         : kind == ENC_EDGE   ? RowTM<P, ENC_EDGE, L, D>::value
+         : kind == NODE_BLOCK ? RowTM<P, NODE_BLOCK, L, D>::value
+                              : RowTM<P, DECODER, L, D>::value;
+}
+
+int rows_bwd_grid(int prec, int L, int D, int kind, int64_t rows, int grid) {
+  if (rows_rs(prec, L, D, kind) || rows_rt_bwd(prec, L, D, kind, false) || rows_rw(prec, L, D, kind)) return RS_GRID;
+  int tm = 16;
+#define RG(PP, LL, DD) \
+  if (prec == PP && L == LL && D == DD) tm = rows_bwd_tile<PP, LL, DD>(kind);
+  RG(F32, 64, 2) RG(F32, 64, 3) RG(F32, 128, 2) RG(F32, 128, 3) RG(F32, 256, 2) RG(F32, 256, 3)
+  RG(BF16, 64, 2) RG(BF16, 64, 3) RG(BF16, 128, 2) RG(BF16, 128, 3) RG(BF16, 256, 2) RG(BF16, 256, 3)
+#undef RG
+  const int64_t tiles = (rows + tm - 1) / tm;  // no workgroup (and no partial to add) without a tile
+  return (int)(tiles < 1 ? 1 : tiles < grid ? tiles : grid);
 }
 
 template <int L, int KIND>
@@ -6295,32 +6082,15 @@ hipError_t launch_input_grad(int prec, int L, const InGradArgs& a, hipStream_t s
   return hipErrorInvalidValue;
 }
 
-int dw_splits(int64_t R, int O, int I) {
-  const int64_t tiles = (int64_t)((O + DW_TO - 1) / DW_TO) * ((I + DW_TI - 1) / DW_TI);
-  int64_t s = 2048 / tiles;
-  const int64_t by_rows = (R + 4 * DW_RC - 1) / (4 * DW_RC);  // at least 4 chunks per split
-  if (s > by_rows) s = by_rows;
-  if (s < 1) s = 1;
-  return (int)s;
-}
-
-hipError_t launch_dw(int prec, const DwArgs& a, hipStream_t st) {
-  dim3 grid((a.O + DW_TO - 1) / DW_TO, (a.I + DW_TI - 1) / DW_TI, a.S);
-  if (a.d_kind == 1 && (a.O % 8 != 0 || a.ldd % 8 != 0)) return hipErrorInvalidValue;
-  if (prec == F32)
-    hipLaunchKernelGGL((dw_kernel<F32, false>), grid, dim3(NT), 0, st, a);
-  else if (a.d_kind == 1)
-    hipLaunchKernelGGL((dw_kernel<BF16, true>), grid, dim3(NT), 0, st, a);
-  else
-    hipLaunchKernelGGL((dw_kernel<BF16, false>), grid, dim3(NT), 0, st, a);
-  return hipGetLastError();
-}
-
 int dw_stream_parts() { return DWS_WAVES; }
+
+// Rows from which an fp32 128 x 128 layer takes a launch of its own: there the
+// single read of each operand outweighs its 64 MiB of partials.
+constexpr int64_t DWS_F32_ROWS = 1 << 18;
 
 bool dw_stream_f32_ok(int prec, const DwArgs& a) {
   return prec == F32 && a.a_kind == 0 && a.d_kind == 0 && a.O == 128 && a.I == 128 && a.ldd % 4 == 0 &&
-         a.lda0 % 4 == 0 && a.R >= 8192 && ((uintptr_t)a.delta % 16) == 0 && ((uintptr_t)a.a0 % 16) == 0;
+         a.lda0 % 4 == 0 && a.R >= DWS_F32_ROWS && ((uintptr_t)a.delta % 16) == 0 && ((uintptr_t)a.a0 % 16) == 0;
 }
 
 hipError_t launch_dw_stream_f32(const DwArgs& a, float* dst, int ldw, int accumulate, hipStream_t st) {
@@ -6384,16 +6154,6 @@ hipError_t launch_dw_reduce(const float* part, int S, int O, int I, float* dst, 
                             hipStream_t st) {
   const int64_t n = (int64_t)O * I;
   hipLaunchKernelGGL(dw_reduce_kernel, dim3((unsigned)((n + 63) / 64)), dim3(NT), 0, st, part, S, O, I, dst, ldw,
-                     accumulate);
-  return hipGetLastError();
-}
-
-hipError_t launch_vec_reduce(const float* vpart, int nwg, int nvec, const VecSeg* segs, int nseg, float* dparams,
-                             int accumulate, hipStream_t st) {
-  VecSegs s;
-  s.n = nseg;
-  for (int i = 0; i < nseg && i < 4; ++i) s.s[i] = segs[i];
-  hipLaunchKernelGGL(vec_reduce_kernel, dim3((nvec + 63) / 64), dim3(NT), 0, st, vpart, nwg, nvec, s, dparams,
                      accumulate);
   return hipGetLastError();
 }
