@@ -980,10 +980,10 @@ struct Bwd {
     a.fout = m->cfg.node_out;
     {
       Timed t_(m, MGN_T_NODE_BWD, st);
-      e = launch_rows_bwd(m->prec, L, D, DECODER, a, rows_bwd_grid(m->prec, L, D, DECODER, no, BWD_GRID), st);
+      e = launch_rows_bwd(m->prec, L, D, DECODER, a, rows_bwd_grid(m->prec, L, D, DECODER, 0, no, BWD_GRID), st);
     }
     CHK("decoder");
-    e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, DECODER, no, BWD_GRID));
+    e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, DECODER, 0, no, BWD_GRID));
     CHK("decoder vec");
     DwArgs w{};
     w.delta = DEL_N[0];
@@ -1061,10 +1061,10 @@ struct Bwd {
       a.dx1 = DAGG;
       {
         Timed t_(m, MGN_T_NODE_BWD, st);
-        e = launch_rows_bwd(m->prec, L, D, NODE_BLOCK, a, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, no, BWD_GRID), st);
+        e = launch_rows_bwd(m->prec, L, D, NODE_BLOCK, a, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, 0, no, BWD_GRID), st);
       }
       CHK("node block");
-      e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, no, BWD_GRID));
+      e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, NODE_BLOCK, 0, no, BWD_GRID));
       CHK("node vec");
       // first Linear, input [v | agg]: one weight gradient per column block
       // (each a plain row-major operand, so the register-resident kernels
@@ -1218,10 +1218,10 @@ struct Bwd {
       a.dm = DV[a_];
       {
         Timed t_(m, MGN_T_NODE_BWD, st);
-        e = launch_rows_bwd(m->prec, L, D, ENC_NODE, a, rows_bwd_grid(m->prec, L, D, ENC_NODE, no, BWD_GRID), st);
+        e = launch_rows_bwd(m->prec, L, D, ENC_NODE, a, rows_bwd_grid(m->prec, L, D, ENC_NODE, m->cfg.node_in, no, BWD_GRID), st);
       }
       CHK("EncNode");
-      e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, ENC_NODE, no, BWD_GRID));
+      e = run_vec(ml, VP, accumulate, rows_bwd_grid(m->prec, L, D, ENC_NODE, m->cfg.node_in, no, BWD_GRID));
       CHK("EncNode vec");
       DwArgs w{};
       w.delta = DEL_N[0];
@@ -1250,14 +1250,14 @@ struct Bwd {
         else a.dm = (const float*)DE + (size_t)e0 * L;
         // narrow features: the kernel forms the first Linear's weight
         // gradient itself (per-wave partials) instead of storing dz_0
-        const int w1s = rows > 0 ? rows_rt_w1_parts(m->prec, L, D, ENC_EDGE, a.fin) : 0;
+        const int w1s = rows > 0 ? rows_rt_w1_parts(m->prec, L, D, ENC_EDGE, a.fin, rows) : 0;
         if (w1s) a.w1_part = (float*)(ws + p.PART);
         {
           Timed t_(m, MGN_T_NODE_BWD, st);
-          e = launch_rows_bwd(m->prec, L, D, ENC_EDGE, a, rows_bwd_grid(m->prec, L, D, ENC_EDGE, rows, BWD_GRID), st);
+          e = launch_rows_bwd(m->prec, L, D, ENC_EDGE, a, rows_bwd_grid(m->prec, L, D, ENC_EDGE, m->cfg.edge_in, rows, BWD_GRID), st);
         }
         CHK("EncEdge");
-        e = run_vec(ml, VPE, acc, rows_bwd_grid(m->prec, L, D, ENC_EDGE, rows, BWD_GRID));
+        e = run_vec(ml, VPE, acc, rows_bwd_grid(m->prec, L, D, ENC_EDGE, m->cfg.edge_in, rows, BWD_GRID));
         CHK("EncEdge vec");
         if (w1s) {
           Timed t_(m, MGN_T_WEIGHT_GRAD, st);

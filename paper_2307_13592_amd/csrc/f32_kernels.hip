@@ -38,19 +38,19 @@ constexpr int TF_NWV = 8, TF_NTH = 64 * TF_NWV;
 // every bank once.
 __device__ __forceinline__ int tf_slot(int i, int q) { return 16 * q + (i ^ q); }
 
-// Copies NB 16-column blocks x NB k-groups of packed fragments (source block
+// Copies NB 16-column blocks x NK k-groups of packed fragments (source block
 // stride SRC k-groups, first k-group kg0) into LDS in tf_slot order, NTH
 // threads, the loads of up to eight fragments per thread in flight.
-template <int NB, int SRC, int NTH>
+template <int NB, int SRC, int NTH, int NK = NB>
 __device__ __forceinline__ void tf_copy_frags(void* dst, const uint4* __restrict__ src, int kg0) {
-  constexpr int TOTAL = NB * NB * 64, IT = (TOTAL + NTH - 1) / NTH, U = IT < 8 ? IT : 8;
+  constexpr int TOTAL = NB * NK * 64, IT = (TOTAL + NTH - 1) / NTH, U = IT < 8 ? IT : 8;
   uint4* d = reinterpret_cast<uint4*>(dst);
   for (int j0 = 0; j0 < IT; j0 += U) {
     uint4 v[U];
 #pragma unroll
     for (int j = 0; j < U; ++j) {
       const int i = threadIdx.x + (j0 + j) * NTH, blk = i >> 6;
-      if (TOTAL % (NTH * U) == 0 || i < TOTAL) v[j] = src[((blk / NB) * SRC + kg0 + blk % NB) * 64 + (i & 63)];
+      if (TOTAL % (NTH * U) == 0 || i < TOTAL) v[j] = src[((blk / NK) * SRC + kg0 + blk % NK) * 64 + (i & 63)];
     }
 #pragma unroll
     for (int j = 0; j < U; ++j) {
@@ -60,18 +60,16 @@ __device__ __forceinline__ void tf_copy_frags(void* dst, const uint4* __restrict
   }
 }
 
-// acc[cb] (+)= sum over k-groups of W[cb][kg] (LDS) x X[kg].
-template <int NB, bool ZERO = true>
-__device__ __forceinline__ void tf_gemm(const float4* Wl, const float4 (&X)[NB], floatx4 (&acc)[NB], int slot) {
-  if constexpr (ZERO) {
+// acc[cb] = sum over k-groups of W[cb][kg] (LDS) x X[kg].
+template <int NB, int NK = NB>
+__device__ __forceinline__ void tf_gemm(const float4* Wl, const float4 (&X)[NK], floatx4 (&acc)[NB], int slot) {
 #pragma unroll
-    for (int cb = 0; cb < NB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-  }
+  for (int cb = 0; cb < NB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int kg = 0; kg < NB; ++kg) {
+  for (int kg = 0; kg < NK; ++kg) {
     float4 w[NB];
 #pragma unroll
-    for (int cb = 0; cb < NB; ++cb) w[cb] = Wl[(cb * NB + kg) * 64 + slot];
+    for (int cb = 0; cb < NB; ++cb) w[cb] = Wl[(cb * NK + kg) * 64 + slot];
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[cb].x, X[kg].x, acc[cb], 0, 0, 0);
 #pragma unroll
@@ -572,6 +570,362 @@ __global__ __launch_bounds__(TF_NTH) void node_proj_f32_kernel(const float* V, c
   }
 }
 
+// --------------------------------------------------------------- row MLPs ---
+// Encoders and the node half of a block.  Their backward has three phases:
+//   A  the first Linear's ReLU output h_1 (from the features, or [v | agg]);
+//   B  the layers after it recomputed, LayerNorm backward, the data gradients
+//      down to dz_0;
+//   C  (node half) dv = dm + dz_0 W_1[:, v-block], dagg = dz_0 W_1[:, agg-block].
+// Phases share a kernel when their weights fit the LDS together (L = 64, and
+// the encoders); the node half at L = 128 (128, 64 and 128 KiB) runs one launch
+// per phase, and what passes between them (h_1, dz_0) is stored for the weight
+// gradients anyway.  NKF: k-groups of an encoder's features (one: at
+// most 16).
+template <int L, int D, int KIND, int NKF, bool A, bool B, bool C>
+struct TfRowsLay {
+  static constexpr int NB = L / 16, W = L * L * 4;
+  static constexpr bool NODE = KIND == NODE_BLOCK;
+  static constexpr int NK1 = NODE ? 2 * NB : NKF;                   // k-groups of the first Linear
+  static constexpr int OFF_WH = A ? NB * NK1 * 1024 : 0;            // D - 1 matrices, the last Linear first
+  static constexpr int OFF_WC = OFF_WH + (B ? (D - 1) * W : 0);
+  static constexpr int OFF_VEC = OFF_WC + (C ? 2 * W : 0);          // b_1, last bias, gamma[, hidden bias]
+  static constexpr int OFF_SCR = OFF_VEC + (D == 3 ? 4 : 3) * L * 4;
+  // ENC_EDGE: dz_0 scratch (16 rows x 32 columns) and the tile's features (4 columns)
+  static constexpr int SCR = 16 * 32 * 4 + 16 * 16;
+  static constexpr int END = OFF_SCR + (KIND == ENC_EDGE ? TF_NWV * SCR : 0);
+  static constexpr int NVEC = (D + 2) * L;
+  static_assert(END <= 160 * 1024 && (!B || TF_NWV * NVEC * 4 <= OFF_VEC), "LDS");
+};
+
+// Features 16 kg + 4 q .. + 3 of a row of fin columns (zero past them).
+template <int NKF>
+__device__ __forceinline__ void tf_features(const float* __restrict__ x, int fin, int q, float4 (&v)[NKF]) {
+#pragma unroll
+  for (int kg = 0; kg < NKF; ++kg) {
+    const int c = 16 * kg + 4 * q;
+    v[kg].x = c < fin ? x[c] : 0.f;
+    v[kg].y = c + 1 < fin ? x[c + 1] : 0.f;
+    v[kg].z = c + 2 < fin ? x[c + 2] : 0.f;
+    v[kg].w = c + 3 < fin ? x[c + 3] : 0.f;
+  }
+}
+
+template <int NB>
+__device__ __forceinline__ uint32_t tf_positive(const float4 (&h)[NB]) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) {
+    m |= (h[cb].x > 0.f ? 1u : 0u) << (4 * cb);
+    m |= (h[cb].y > 0.f ? 1u : 0u) << (4 * cb + 1);
+    m |= (h[cb].z > 0.f ? 1u : 0u) << (4 * cb + 2);
+    m |= (h[cb].w > 0.f ? 1u : 0u) << (4 * cb + 3);
+  }
+  return m;
+}
+
+// Encoder forward: LN(MLP(features)).
+template <int L, int D, int NKF>
+struct TfEncLay {
+  static constexpr int NB = L / 16, W = L * L * 4;
+  static constexpr int OFF_WH = NB * NKF * 1024, OFF_VEC = OFF_WH + (D - 1) * W;
+  static constexpr int END = OFF_VEC + (D == 3 ? 5 : 4) * L * 4;  // b_1, last bias, gamma, beta[, hidden bias]
+  static_assert(END <= 160 * 1024, "LDS");
+};
+template <int L, int D, int NKF>
+__global__ __launch_bounds__(TF_NTH) void enc_fwd_f32_kernel(RowsFwdArgs a) {
+  using Lay = TfEncLay<L, D, NKF>;
+  constexpr int NB = Lay::NB;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float4* W1 = reinterpret_cast<float4*>(lds);
+  float4* WL = reinterpret_cast<float4*>(lds + Lay::OFF_WH);
+  float4* WH = reinterpret_cast<float4*>(lds + Lay::OFF_WH + Lay::W);
+  float* vb1 = reinterpret_cast<float*>(lds + Lay::OFF_VEC);
+  float *vbl = vb1 + L, *vg = vb1 + 2 * L, *vbt = vb1 + 3 * L, *vbh = vb1 + 4 * L;
+  tf_copy_frags<NB, NKF, TF_NTH, NKF>(W1, a.mlp.lin[0].wf, 0);
+  tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
+  if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
+  rt_copy_vec(vb1, a.mlp.lin[0].b, L);
+  rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
+  rt_copy_vec(vg, a.mlp.gamma, L);
+  rt_copy_vec(vbt, a.mlp.beta, L);
+  if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
+  __syncthreads();
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  const int64_t nt = (a.rows + 15) / 16;
+  // tiles go round the workgroups first: few rows still use every CU
+  for (int64_t t = blockIdx.x + (int64_t)gridDim.x * wave; t < nt; t += (int64_t)gridDim.x * TF_NWV) {
+    int ln = lane;  // opaque: the weight fragments are read per tile, not kept in registers
+    asm volatile("" : "+v"(ln));
+    const int e = ln & 15, q = ln >> 4, slot = tf_slot(e, q);
+    const int64_t row = t * 16 + e;
+    const bool ok = row < a.rows;
+    float4 x[NKF];
+    tf_features<NKF>(a.in0 + (ok ? row : t * 16) * a.fin, a.fin, q, x);
+    floatx4 acc[NB];
+    tf_gemm<NB, NKF>(W1, x, acc, slot);
+    float4 h[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vb1, cb, q)));
+    if constexpr (D == 3) {
+      tf_gemm<NB>(WH, h, acc, slot);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vbh, cb, q)));
+    }
+    tf_gemm<NB>(WL, h, acc, slot);
+    float4 y[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) y[cb] = tf_add(acc[cb], rt_ld4(vbl, cb, q));
+    const float mu = rt_sum4(tf_lane_sum<NB>(y)) / L;
+    const float rs = tf_rstd<NB, L>(y, mu, a.eps);
+    if (ok) {
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        const float4 g = rt_ld4(vg, cb, q), bt = rt_ld4(vbt, cb, q);
+        y[cb].x = g.x * ((y[cb].x - mu) * rs) + bt.x;
+        y[cb].y = g.y * ((y[cb].y - mu) * rs) + bt.y;
+        y[cb].z = g.z * ((y[cb].z - mu) * rs) + bt.z;
+        y[cb].w = g.w * ((y[cb].w - mu) * rs) + bt.w;
+      }
+      tf_store<NB>(reinterpret_cast<float*>(a.out) + row * L, q, y);
+    }
+  }
+}
+
+template <int L, int D, int KIND, int NKF, bool A, bool B, bool C>
+__global__ __launch_bounds__(TF_NTH) __attribute__((amdgpu_waves_per_eu(2, 2))) void rows_bwd_f32_kernel(RowsBwdArgs a) {
+  using Lay = TfRowsLay<L, D, KIND, NKF, A, B, C>;
+  constexpr int NB = Lay::NB, NV = 4 * NB, NR = NV / 16, NK1 = Lay::NK1;
+  constexpr bool NODE = Lay::NODE;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float4* W1 = reinterpret_cast<float4*>(lds);
+  float* WL = reinterpret_cast<float*>(lds + Lay::OFF_WH);
+  float* WH = reinterpret_cast<float*>(lds + Lay::OFF_WH + Lay::W);
+  float4* WC = reinterpret_cast<float4*>(lds + Lay::OFF_WC);
+  float* vb1 = reinterpret_cast<float*>(lds + Lay::OFF_VEC);
+  float *vbl = vb1 + L, *vg = vb1 + 2 * L, *vbh = vb1 + 3 * L;
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  if constexpr (A) {
+    tf_copy_frags<NB, NK1, TF_NTH, NK1>(W1, a.mlp.lin[0].wf, 0);
+    rt_copy_vec(vb1, a.mlp.lin[0].b, L);
+  }
+  if constexpr (B) {
+    tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
+    if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
+    rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
+    rt_copy_vec(vg, a.mlp.gamma, L);
+    if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
+  }
+  if constexpr (C) tf_copy_frags<2 * NB, NB, TF_NTH, NB>(WC, a.mlp.lin[0].wb, 0);
+  __syncthreads();
+  // column totals: gamma, beta, last bias, hidden biases
+  constexpr int NQ = 2 + D;
+  float qacc[NQ][NR];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k)
+#pragma unroll
+    for (int t = 0; t < NR; ++t) qacc[k][t] = 0.f;
+  auto coltot = [&](const float4 (&x)[NB], int k, int e) {
+    float f[NV];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) {
+      f[4 * cb] = x[cb].x;
+      f[4 * cb + 1] = x[cb].y;
+      f[4 * cb + 2] = x[cb].z;
+      f[4 * cb + 3] = x[cb].w;
+    }
+    rt_col_totals<NV>(f, e);
+#pragma unroll
+    for (int t = 0; t < NR; ++t) qacc[k][t] += f[t];
+  };
+  // ENC_EDGE with w1_part: the first Linear's weight gradient, columns
+  // lane + 64 j, features 0 .. 3
+  float w1acc[L / 64][4] = {};
+  float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  float4* xs = reinterpret_cast<float4*>(scr + 16 * 32);
+  const int64_t nt = (a.rows + 15) / 16;
+  for (int64_t t = blockIdx.x + (int64_t)gridDim.x * wave; t < nt; t += (int64_t)gridDim.x * TF_NWV) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int e = ln & 15, q = ln >> 4, slot = tf_slot(e, q);
+    const int64_t row = t * 16 + e;
+    const bool ok = row < a.rows;
+    const int64_t src = ok ? row : t * 16;  // rows past the end repeat the tile's first (dm = 0, nothing stored)
+    floatx4 acc[NB];
+    float4 h[NB], dm[NB];
+    if constexpr (A) {
+      float4 x[NK1];
+      if constexpr (NODE) {
+        tf_load<NB>(a.in0 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[0]));
+        tf_load<NB>(a.in1 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[NB]));
+      } else {
+        tf_features<NKF>(a.in0 + src * a.fin, a.fin, q, x);
+        if constexpr (KIND == ENC_EDGE) {
+          if (q == 0) xs[e] = x[0];
+        }
+      }
+      if constexpr (B) tf_load<NB>(a.dm + src * L, q, dm);
+      tf_gemm<NB, NK1>(W1, x, acc, slot);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vb1, cb, q)));
+      if (ok) tf_store<NB>(reinterpret_cast<float*>(a.hid[0]) + row * L, q, h);
+    } else if constexpr (B) {
+      tf_load<NB>(reinterpret_cast<const float*>(a.hid[0]) + src * L, q, h);
+      tf_load<NB>(a.dm + src * L, q, dm);
+    }
+    float4 v[NB];
+    if constexpr (B) {
+      uint32_t mask[2] = {tf_positive<NB>(h), 0u};
+      if constexpr (D == 3) {
+        tf_gemm<NB>(reinterpret_cast<const float4*>(WH), h, acc, slot);
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vbh, cb, q)));
+        mask[1] = tf_positive<NB>(h);
+        if (ok) tf_store<NB>(reinterpret_cast<float*>(a.hid[1]) + row * L, q, h);
+      }
+      tf_gemm<NB>(reinterpret_cast<const float4*>(WL), h, acc, slot);
+      float4 y[NB];
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) y[cb] = tf_add(acc[cb], rt_ld4(vbl, cb, q));
+      if (!ok) {
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) dm[cb] = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      const float mu = rt_sum4(tf_lane_sum<NB>(y)) / L;
+      const float rs = tf_rstd<NB, L>(y, mu, a.eps);
+      // LayerNorm backward: dy = rstd (dm g - mean(dm g) - xhat mean(dm g xhat))
+      float t1, t2;
+      {
+        float4 d1[NB], d2[NB];
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) {
+          const float4 g = rt_ld4(vg, cb, q);
+          y[cb] = make_float4((y[cb].x - mu) * rs, (y[cb].y - mu) * rs, (y[cb].z - mu) * rs, (y[cb].w - mu) * rs);
+          d1[cb] = make_float4(dm[cb].x * g.x, dm[cb].y * g.y, dm[cb].z * g.z, dm[cb].w * g.w);
+          d2[cb] = make_float4(d1[cb].x * y[cb].x, d1[cb].y * y[cb].y, d1[cb].z * y[cb].z, d1[cb].w * y[cb].w);
+        }
+        t1 = rt_sum4(tf_lane_sum<NB>(d1)) / L;
+        t2 = rt_sum4(tf_lane_sum<NB>(d2)) / L;
+      }
+      coltot(dm, 1, e);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        const float4 g = rt_ld4(vg, cb, q);
+        v[cb].x = rs * (dm[cb].x * g.x - t1 - y[cb].x * t2);
+        v[cb].y = rs * (dm[cb].y * g.y - t1 - y[cb].y * t2);
+        v[cb].z = rs * (dm[cb].z * g.z - t1 - y[cb].z * t2);
+        v[cb].w = rs * (dm[cb].w * g.w - t1 - y[cb].w * t2);
+        // gamma's column terms
+        y[cb] = make_float4(dm[cb].x * y[cb].x, dm[cb].y * y[cb].y, dm[cb].z * y[cb].z, dm[cb].w * y[cb].w);
+      }
+      if (ok) tf_store<NB>(reinterpret_cast<float*>(a.delta[D - 1]) + row * L, q, v);
+      coltot(y, 0, e);
+      coltot(v, 2, e);
+      int tb[4];
+      tf_t_index(e, q, tb);
+#pragma unroll
+      for (int j = D - 1; j >= 1; --j) {
+        tf_gemm_t<NB>(j == D - 1 ? WL : WH, v, acc, tb);
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) {
+          const uint32_t mk = mask[j - 1] >> (4 * cb);
+          v[cb] = make_float4(mk & 1u ? acc[cb][0] : 0.f, mk & 2u ? acc[cb][1] : 0.f, mk & 4u ? acc[cb][2] : 0.f,
+                              mk & 8u ? acc[cb][3] : 0.f);
+        }
+        if ((KIND != ENC_EDGE || j > 1 || !a.w1_part) && ok)
+          tf_store<NB>(reinterpret_cast<float*>(a.delta[j - 1]) + row * L, q, v);
+        coltot(v, 2 + j, e);
+      }
+      if constexpr (KIND == ENC_EDGE) {
+        if (a.w1_part) {
+          // dW_1 += dz_0^T x over the tile's rows (zero past its end), in row
+          // order; the scratch passes 32 columns at a time (tf_segment_sums)
+#pragma unroll
+          for (int j = 0; j < L / 64; ++j) {
+            float z[16];
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll
+              for (int c = 0; c < 2; ++c)
+                *reinterpret_cast<float4*>(scr + rs_sw32<32>(e, c * 16 + q * 4)) = v[4 * j + 2 * half + c];
+              if ((ln >> 5) == half) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) z[r] = scr[rs_sw32<32>(r, ln & 31)];
+              }
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float4 x = xs[r];
+              w1acc[j][0] = fmaf(z[r], x.x, w1acc[j][0]);
+              w1acc[j][1] = fmaf(z[r], x.y, w1acc[j][1]);
+              w1acc[j][2] = fmaf(z[r], x.z, w1acc[j][2]);
+              w1acc[j][3] = fmaf(z[r], x.w, w1acc[j][3]);
+            }
+          }
+        }
+      }
+    }
+    if constexpr (C) {
+      if constexpr (!B) {
+        tf_load<NB>(reinterpret_cast<const float*>(a.delta[0]) + src * L, q, v);
+        tf_load<NB>(a.dm + src * L, q, dm);
+      }
+#pragma unroll
+      for (int pass = 0; pass < 2; ++pass) {
+        tf_gemm<NB>(WC + pass * NB * NB * 64, v, acc, slot);
+        if (ok) {
+          float* o = (pass == 0 ? a.dx0 : a.dx1) + row * L;
+#pragma unroll
+          for (int cb = 0; cb < NB; ++cb)
+            *reinterpret_cast<float4*>(o + cb * 16 + q * 4) =
+                pass == 0 ? tf_add(acc[cb], dm[cb]) : make_float4(acc[cb][0], acc[cb][1], acc[cb][2], acc[cb][3]);
+        }
+      }
+    }
+  }
+  if constexpr (B) {
+    // column partials (edge_bwd_f32_kernel), then the fused weight gradient,
+    // summed over the waves in order
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(lds);
+    {
+      float* rw = red + wave * Lay::NVEC;
+#pragma unroll
+      for (int t = 0; t < NR; ++t) {
+        const int i = (lane & 15) * NR + t;
+        const int col = (i >> 2) * 16 + (lane >> 4) * 4 + (i & 3);
+#pragma unroll
+        for (int h = 0; h < D - 1; ++h) rw[h * L + col] = qacc[3 + h][t];
+        rw[(D - 1) * L + col] = qacc[2][t];
+        rw[D * L + col] = qacc[0][t];
+        rw[(D + 1) * L + col] = qacc[1][t];
+      }
+    }
+    __syncthreads();
+    float* vp = a.vpart + (int64_t)blockIdx.x * a.nvec;
+    for (int i = threadIdx.x; i < Lay::NVEC; i += TF_NTH) {
+      float s = 0.f;
+      for (int w = 0; w < TF_NWV; ++w) s += red[w * Lay::NVEC + i];
+      vp[i] = s;
+    }
+    if constexpr (KIND == ENC_EDGE) {
+      if (a.w1_part) {
+        static_assert(TF_NWV * L * 16 <= Lay::OFF_VEC, "LDS");
+        __syncthreads();
+        float4* rw = reinterpret_cast<float4*>(lds);
+#pragma unroll
+        for (int j = 0; j < L / 64; ++j)
+          rw[wave * L + lane + 64 * j] = make_float4(w1acc[j][0], w1acc[j][1], w1acc[j][2], w1acc[j][3]);
+        __syncthreads();
+        for (int i = threadIdx.x; i < 4 * L; i += TF_NTH) {
+          float s = 0.f;
+          for (int w = 0; w < TF_NWV; ++w) s += red[w * 4 * L + i];
+          if ((i & 3) < a.fin) a.w1_part[(int64_t)blockIdx.x * L * a.fin + (i >> 2) * a.fin + (i & 3)] = s;
+        }
+      }
+    }
+  }
+}
+
 template <class F>
 void allow_lds(F* fn, int bytes) {
   if (bytes > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
@@ -613,7 +967,70 @@ hipError_t node_proj_f32_t(const float* V, const float* H, int64_t n_owned, int6
   return hipGetLastError();
 }
 
+int tf_rows_grid(int64_t rows) {
+  const int64_t t = (rows + 15) / 16;
+  return (int)(t < 1 ? 1 : t < RS_GRID ? t : RS_GRID);
+}
+
+template <int L, int D, int NKF>
+hipError_t enc_fwd_f32_t(const RowsFwdArgs& a, hipStream_t st) {
+  using Lay = TfEncLay<L, D, NKF>;
+  allow_lds(enc_fwd_f32_kernel<L, D, NKF>, Lay::END);
+  hipLaunchKernelGGL((enc_fwd_f32_kernel<L, D, NKF>), dim3(tf_rows_grid(a.rows)), dim3(TF_NTH), Lay::END, st, a);
+  return hipGetLastError();
+}
+
+template <int L, int D, int KIND, int NKF, bool A, bool B, bool C>
+hipError_t rows_bwd_f32_t(const RowsBwdArgs& a, hipStream_t st) {
+  using Lay = TfRowsLay<L, D, KIND, NKF, A, B, C>;
+  allow_lds(rows_bwd_f32_kernel<L, D, KIND, NKF, A, B, C>, Lay::END);
+  hipLaunchKernelGGL((rows_bwd_f32_kernel<L, D, KIND, NKF, A, B, C>), dim3(tf_rows_grid(a.rows)), dim3(TF_NTH), Lay::END,
+                     st, a);
+  return hipGetLastError();
+}
+
+template <int L, int D>
+hipError_t rows_bwd_f32_d(int kind, const RowsBwdArgs& a, hipStream_t st) {
+  if (kind == NODE_BLOCK) {
+    if constexpr (L == 64) {
+      return rows_bwd_f32_t<L, D, NODE_BLOCK, 1, true, true, true>(a, st);
+    } else {
+      hipError_t e = rows_bwd_f32_t<L, D, NODE_BLOCK, 1, true, false, false>(a, st);
+      if (e == hipSuccess) e = rows_bwd_f32_t<L, D, NODE_BLOCK, 1, false, true, false>(a, st);
+      if (e == hipSuccess) e = rows_bwd_f32_t<L, D, NODE_BLOCK, 1, false, false, true>(a, st);
+      return e;
+    }
+  }
+  if (kind == ENC_EDGE)
+    return a.fin <= 16 ? rows_bwd_f32_t<L, D, ENC_EDGE, 1, true, true, false>(a, st) : hipErrorInvalidValue;
+  return a.fin <= 16 ? rows_bwd_f32_t<L, D, ENC_NODE, 1, true, true, false>(a, st) : hipErrorInvalidValue;
+}
+
 }  // namespace
+
+bool rows_f32(int prec, int L, int D, int kind, int fin) {
+  if (prec != F32 || (L != 64 && L != 128)) return false;
+  return kind == NODE_BLOCK || ((kind == ENC_NODE || kind == ENC_EDGE) && fin <= 16);
+}
+// (128, 3) keeps the other forward, as its edge half does: one pass per step
+// beside a streaming edge forward of many times its work.
+bool enc_fwd_f32(int prec, int L, int D, int kind, int fin) {
+  return kind != NODE_BLOCK && rows_f32(prec, L, D, kind, fin) && edge_f32(prec, L, D);
+}
+int rows_f32_grid(int64_t rows) { return tf_rows_grid(rows); }
+int rows_f32_w1_parts(int64_t rows, int kind, int fin) { return kind == ENC_EDGE && fin <= 4 ? tf_rows_grid(rows) : 0; }
+
+hipError_t launch_enc_fwd_f32(int L, int D, const RowsFwdArgs& a, hipStream_t st) {
+  if (a.rows == 0) return hipSuccess;
+  if (L == 64) return D == 2 ? enc_fwd_f32_t<64, 2, 1>(a, st) : enc_fwd_f32_t<64, 3, 1>(a, st);
+  if (L == 128 && D == 2) return enc_fwd_f32_t<128, 2, 1>(a, st);
+  return hipErrorInvalidValue;
+}
+hipError_t launch_rows_bwd_f32(int L, int D, int kind, const RowsBwdArgs& a, hipStream_t st) {
+  if (L == 64) return D == 2 ? rows_bwd_f32_d<64, 2>(kind, a, st) : rows_bwd_f32_d<64, 3>(kind, a, st);
+  if (L == 128) return D == 2 ? rows_bwd_f32_d<128, 2>(kind, a, st) : rows_bwd_f32_d<128, 3>(kind, a, st);
+  return hipErrorInvalidValue;
+}
 
 bool edge_f32(int prec, int L, int D) { return prec == F32 && (L == 64 || (L == 128 && D == 2)); }
 

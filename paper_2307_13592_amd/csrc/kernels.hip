@@ -328,10 +328,10 @@ __global__ void pack_kernel(const float* __restrict__ W, int out, int in, int bw
   for (int e = 0; e < P::EL; ++e) {
     const int k = k0 + e;
     float x = 0.f;
-    if (!bwd) {
-      if (j < out && k < in) x = W[(int64_t)j * in + k];
+    if (!jb.bwd) {
+      if (j < jb.out && k < jb.in) x = W[(int64_t)j * jb.in + k];
     } else {
-      if (j < in && k < out) x = W[(int64_t)k * in + j];
+      if (j < jb.in && k < jb.out) x = W[(int64_t)k * jb.in + j];
     }
     v[e] = P::cvt(x);
   }
@@ -5804,14 +5804,16 @@ static hipError_t rows_rt_bwd_t(const RowsBwdArgs& a, hipStream_t st) {
 static_assert((int64_t)RS_GRID * RtRowsLay<128, ENC_EDGE>::NWV * 128 * RtRowsLay<128, ENC_EDGE>::W1_FIN <=
                   (int64_t)DWS_WAVES * 16384,
               "w1 partials");
-int rows_rt_w1_parts(int prec, int L, int D, int kind, int fin) {
+int rows_rt_w1_parts(int prec, int L, int D, int kind, int fin, int64_t rows) {
   if (kind != ENC_EDGE || fin < 1) return 0;
+  if (rows_f32(prec, L, D, kind, fin)) return rows_f32_w1_parts(rows, kind, fin);
   if (rows_rw(prec, L, D, kind)) return fin <= RW_ENC_FIN ? RS_GRID * RwEncBwdLay<3>::NWV : 0;
   if (!rows_rt(prec, L, D, kind) || fin > RtRowsLay<128, ENC_EDGE>::W1_FIN) return 0;
   return RS_GRID * RtRowsLay<128, ENC_EDGE>::NWV;
 }
 
 hipError_t launch_rows_fwd(int prec, int L, int D, int kind, const RowsFwdArgs& a, hipStream_t st) {
+  if (enc_fwd_f32(prec, L, D, kind, a.fin)) return launch_enc_fwd_f32(L, D, a, st);
   if (rows_rw(prec, L, D, kind)) {
     if (kind == ENC_EDGE) return D == 2 ? rows_rw_enc_fwd_t<2>(a, st) : rows_rw_enc_fwd_t<3>(a, st);
     return D == 2 ? rows_rw_fwd_t<2>(a, st) : rows_rw_fwd_t<3>(a, st);
@@ -5861,7 +5863,8 @@ static int rows_bwd_tile(int kind) {
                               : RowTM<P, DECODER, L, D>::value;
 }
 
-int rows_bwd_grid(int prec, int L, int D, int kind, int64_t rows, int grid) {
+int rows_bwd_grid(int prec, int L, int D, int kind, int fin, int64_t rows, int grid) {
+  if (rows_f32(prec, L, D, kind, fin)) return rows_f32_grid(rows);
   if (rows_rs(prec, L, D, kind) || rows_rt_bwd(prec, L, D, kind, false) || rows_rw(prec, L, D, kind)) return RS_GRID;
   int tm = 16;
 #define RG(PP, LL, DD) \
@@ -5882,6 +5885,7 @@ static hipError_t rows_bwd_rs_t(const RowsBwdArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_rows_bwd(int prec, int L, int D, int kind, const RowsBwdArgs& a, int grid, hipStream_t st) {
+  if (rows_f32(prec, L, D, kind, a.fin)) return launch_rows_bwd_f32(L, D, kind, a, st);
   if (rows_rw(prec, L, D, kind)) {
     if (kind == ENC_EDGE) return D == 2 ? rows_rw_enc_bwd_t<2>(a, st) : rows_rw_enc_bwd_t<3>(a, st);
     return D == 2 ? rows_rw_bwd_t<2>(a, st) : rows_rw_bwd_t<3>(a, st);
@@ -5903,7 +5907,9 @@ hipError_t launch_rows_bwd(int prec, int L, int D, int kind, const RowsBwdArgs& 
     switch (kind) {                                                                         \
       case ENC_NODE: return rows_bwd_t<PP, LL, DD, ENC_NODE>(a, grid, st);                  \
       case ENC_EDGE: return rows_bwd_t<PP, LL, DD, ENC_EDGE>(a, grid, st);                  \
-      case NODE_BLOCK: return rows_bwd_t<PP, LL, DD, NODE_BLOCK>(a, grid, st);              \
+      case NODE_BLOCK:                                                                      \
+        if constexpr (PP == F32 && LL < 256) return hipErrorInvalidValue; /* rows_f32 */    \
+        else return rows_bwd_t<PP, LL, DD, NODE_BLOCK>(a, grid, st);                        \
       default: return rows_bwd_t<PP, LL, DD, DECODER>(a, grid, st);                         \
     }                                                                                       \
   }
