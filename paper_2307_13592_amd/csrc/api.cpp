@@ -68,6 +68,8 @@ struct mgn_model {
   float* params = nullptr;
   uint4* packed = nullptr;
   size_t packed_n = 0;
+  std::vector<PackJob> pack;       // every packed copy
+  PackJob* pack_dev = nullptr;     // the same in device memory
   bool params_set = false;
   // graph accepted by mgn_graph_validate, and a host copy of its row_ptr
   bool graph_ok = false;
@@ -135,14 +137,7 @@ namespace {
 
 // Refreshes the packed copies of every Linear's weights from the fp32 master copy.
 hipError_t repack(mgn_model* m, hipStream_t st) {
-  for (const MlpL& ml : m->mlp)
-    for (int j = 0; j < ml.depth; ++j) {
-      const LinL& L = ml.lin[j];
-      hipError_t e = launch_pack(m->prec, m->params + L.w, L.out, L.in, 0, m->packed + L.pf, L.nkgf, st);
-      if (e == hipSuccess) e = launch_pack(m->prec, m->params + L.w, L.out, L.in, 1, m->packed + L.pb, L.nkgb, st);
-      if (e != hipSuccess) return e;
-    }
-  return hipSuccess;
+  return launch_pack(m->prec, m->pack_dev, (int)m->pack.size(), (int64_t)m->packed_n, m->params, m->packed, st);
 }
 
 size_t tsize(const mgn_model* m) { return m->prec == BF16 ? 2 : 4; }
@@ -191,8 +186,10 @@ MlpL make_mlp(mgn_model* m, int fin, int fout, bool ln, int64_t& off, size_t& po
     L.nkgf = (L.in + m->kg - 1) / m->kg;
     L.nkgb = (L.out + m->kg - 1) / m->kg;
     L.pf = poff;
+    m->pack.push_back(PackJob{L.w, (int64_t)poff, (int64_t)poff, L.out, L.in, L.nkgf, 0});
     poff += (size_t)((L.out + 15) / 16) * L.nkgf * 64;
     L.pb = poff;
+    m->pack.push_back(PackJob{L.w, (int64_t)poff, (int64_t)poff, L.out, L.in, L.nkgb, 1});
     poff += (size_t)((L.in + 15) / 16) * L.nkgb * 64;
     prev = L.out;
   }
@@ -395,6 +392,7 @@ void mgn_destroy(mgn_model* m) {
   for (hipEvent_t e : m->ev_pool) (void)hipEventDestroy(e);
   if (m->params) (void)hipFree(m->params);
   if (m->packed) (void)hipFree(m->packed);
+  if (m->pack_dev) (void)hipFree(m->pack_dev);
   delete m;
 }
 
@@ -407,10 +405,16 @@ mgn_status mgn_set_params(mgn_model* m, const float* src, int src_on_device, mgn
   if (!m->params) {
     hipError_t a = hipMalloc(&m->params, sizeof(float) * m->P);
     if (a == hipSuccess) a = hipMalloc(&m->packed, sizeof(uint4) * m->packed_n);
+    if (a == hipSuccess) a = hipMalloc(&m->pack_dev, sizeof(PackJob) * m->pack.size());
+    if (a == hipSuccess)
+      a = hipMemcpy(m->pack_dev, m->pack.data(), sizeof(PackJob) * m->pack.size(), hipMemcpyHostToDevice);
     if (a != hipSuccess) {
       if (m->params) (void)hipFree(m->params);
+      if (m->packed) (void)hipFree(m->packed);
+      if (m->pack_dev) (void)hipFree(m->pack_dev);
       m->params = nullptr;
       m->packed = nullptr;
+      m->pack_dev = nullptr;
       return fail(m, MGN_E_NOMEM, std::string("mgn_set_params: ") + hipGetErrorString(a));
     }
   }

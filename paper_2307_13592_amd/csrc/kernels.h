@@ -181,7 +181,16 @@ hipError_t launch_norm_apply(const float* x, int64_t rows, int cols, const doubl
 // aligned rows); pairs with out-of-range indices are skipped.
 hipError_t launch_rows_copy(const float* src, int64_t n_src, const int32_t* src_rows, const int32_t* dst_rows,
                             int64_t n, int L, float* dst, int64_t n_dst, int add, hipStream_t st);
-hipError_t launch_pack(int prec, const float* W, int out, int in, int bwd, uint4* dst, int nkg, hipStream_t st);
+// One packed copy of a Linear's weights: W at params + w -> packed + dst,
+// (bwd) the backward layout; its 16-byte fragments are the entries [first,
+// first + blocks * nkg * 64) of all copies.
+struct PackJob {
+  int64_t w, dst, first;
+  int32_t out, in, nkg, bwd;
+};
+// Refreshes all copies (jobs: n entries in device memory, total fragments).
+hipError_t launch_pack(int prec, const PackJob* jobs, int n, int64_t total, const float* params, uint4* packed,
+                       hipStream_t st);
 hipError_t launch_erecv(const int32_t* row_ptr, int64_t n_owned, int32_t* erecv, hipStream_t st);
 hipError_t launch_plan(const int32_t* row_ptr, int64_t n_owned, int te_target, int r_max, int32_t* chunk_cnt,
                        int32_t* unit_r, int32_t* n_units, hipStream_t st);

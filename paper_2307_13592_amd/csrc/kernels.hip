@@ -313,14 +313,25 @@ __device__ __forceinline__ float to_f(float x) { return x; }
 __device__ __forceinline__ float to_f(uint16_t x) { return bf2f(x); }
 
 // ----------------------------------------------------------------- pack ---
+// All packed copies in one launch: after every update each of some 120 copies
+// was a launch of its own (2.7 us each, 0.43 ms of a 15-block step).
 template <class P>
-__global__ void pack_kernel(const float* __restrict__ W, int out, int in, int bwd, uint4* __restrict__ dst,
-                            int nkg, int64_t total) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
+__global__ void pack_kernel(const PackJob* __restrict__ jobs, int n, int64_t total, const float* __restrict__ params,
+                            uint4* __restrict__ packed) {
+  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (at >= total) return;
+  int lo = 0, hi = n - 1;  // the last job that starts at or before `at`
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (jobs[mid].first <= at) lo = mid;
+    else hi = mid - 1;
+  }
+  const PackJob jb = jobs[lo];
+  const float* W = params + jb.w;
+  const int64_t idx = at - jb.first;
   const int lane = (int)(idx & 63);
-  const int kg = (int)((idx >> 6) % nkg);
-  const int nb = (int)((idx >> 6) / nkg);
+  const int kg = (int)((idx >> 6) % jb.nkg);
+  const int nb = (int)((idx >> 6) / jb.nkg);
   const int j = nb * 16 + (lane & 15);
   const int k0 = kg * P::KG + (lane >> 4) * P::EL;
   typename P::T v[P::EL];
@@ -335,7 +346,7 @@ __global__ void pack_kernel(const float* __restrict__ W, int out, int in, int bw
     }
     v[e] = P::cvt(x);
   }
-  dst[idx] = *reinterpret_cast<const uint4*>(v);
+  packed[jb.dst + idx] = *reinterpret_cast<const uint4*>(v);
 }
 
 // ------------------------------------------------------------- fills ---
@@ -5631,14 +5642,11 @@ int edge_tile_rows(int prec, int L, int D) {
   return 0;
 }
 
-hipError_t launch_pack(int prec, const float* W, int out, int in, int bwd, uint4* dst, int nkg, hipStream_t st) {
-  const int nblk = ((bwd ? in : out) + 15) / 16;
-  const int64_t total = (int64_t)nblk * nkg * 64;
-  const int grid = (int)((total + NT - 1) / NT);
-  if (prec == F32)
-    hipLaunchKernelGGL(pack_kernel<PF32>, dim3(grid), dim3(NT), 0, st, W, out, in, bwd, dst, nkg, total);
-  else
-    hipLaunchKernelGGL(pack_kernel<PBF16>, dim3(grid), dim3(NT), 0, st, W, out, in, bwd, dst, nkg, total);
+hipError_t launch_pack(int prec, const PackJob* jobs, int n, int64_t total, const float* params, uint4* packed,
+                       hipStream_t st) {
+  const unsigned grid = (unsigned)((total + NT - 1) / NT);
+  if (prec == F32) hipLaunchKernelGGL(pack_kernel<PF32>, dim3(grid), dim3(NT), 0, st, jobs, n, total, params, packed);
+  else hipLaunchKernelGGL(pack_kernel<PBF16>, dim3(grid), dim3(NT), 0, st, jobs, n, total, params, packed);
   return hipGetLastError();
 }
 
