@@ -926,20 +926,268 @@ __global__ __launch_bounds__(TF_NTH) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   }
 }
 
+// Few rows: a wave per (16-row tile, group of CB output column blocks), its
+// weights read straight from the packed copy.  A tile's whole product keeps
+// one SIMD's matrix pipe busy for 7.8 us at 3 L x L (L = 128), and with under
+// TF_COLS_TILES tiles most SIMDs have none; this way neighbouring waves share
+// a tile, and no workgroup waits for 64 - 128 KiB of weights to reach its LDS.
+constexpr int TF_COLS_TILES = 512;
+
+// acc[c] = sum over k-groups of W[cb0 + c][kg0 + kg] x X[kg]; W: packed, SRC
+// k-groups per block.
+template <int CB, int NK, int SRC>
+__device__ __forceinline__ void tf_gemm_cols(const uint4* __restrict__ W, int cb0, int kg0, const float4 (&X)[NK],
+                                             floatx4 (&acc)[CB], int lane) {
+  const float4* Wl = reinterpret_cast<const float4*>(W) + lane;
+  float4 w[CB][NK];
+#pragma unroll
+  for (int kg = 0; kg < NK; ++kg)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) w[c][kg] = Wl[((cb0 + c) * SRC + kg0 + kg) * 64];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kg = 0; kg < NK; ++kg) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][kg].x, X[kg].x, acc[c], 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][kg].y, X[kg].y, acc[c], 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][kg].z, X[kg].z, acc[c], 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[c][kg].w, X[kg].w, acc[c], 0, 0, 0);
+  }
+}
+
+// node_proj_f32_kernel for few rows: units (tile, side, column group); halo
+// tiles after the owned ones, sender side only.
+template <int L>
+__global__ __launch_bounds__(256) void node_proj_cols_kernel(const float* V, const float* H, int64_t n_owned,
+                                                             int64_t n_halo, Lin w1, float* ps, float* ps_halo,
+                                                             float* pr) {
+  constexpr int NB = L / 16, CB = 2, G = NB / CB;
+  const int lane = threadIdx.x & 63, e = lane & 15, q = lane >> 4;
+  const int to = (int)((n_owned + 15) / 16), th = (int)((n_halo + 15) / 16);
+  const int u = blockIdx.x * 4 + wave_id();
+  if (u >= (2 * to + th) * G) return;
+  const int cb0 = u % G * CB, ts = u / G;
+  const bool halo = ts >= 2 * to;
+  const int side = halo ? 0 : ts & 1;
+  const int64_t row0 = (int64_t)(halo ? ts - 2 * to : ts >> 1) * 16, row = row0 + e;
+  const bool ok = row < (halo ? n_halo : n_owned);
+  float4 x[NB];
+  tf_load<NB>((halo ? H : V) + (ok ? row : row0) * L, q, x);
+  floatx4 acc[CB];
+  tf_gemm_cols<CB, NB, 3 * NB>(w1.wf, cb0, (1 + side) * NB, x, acc, lane);
+  if (ok) {
+    float* o = (side ? pr : halo ? ps_halo : ps) + row * L;
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      float4 v = make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
+      if (side) v = tf_add(acc[c], rt_ld4(w1.b, cb0 + c, q));
+      *reinterpret_cast<float4*>(o + (cb0 + c) * 16 + q * 4) = v;
+    }
+  }
+}
+
+// Phases A and C of the node half's backward (rows_bwd_f32_kernel) for few rows.
+template <int L, bool PHASE_C>
+__global__ __launch_bounds__(256) void node_bwd_cols_kernel(RowsBwdArgs a) {
+  constexpr int NB = L / 16, CB = 2, G = (PHASE_C ? 2 * NB : NB) / CB;
+  const int lane = threadIdx.x & 63, e = lane & 15, q = lane >> 4;
+  const int u = blockIdx.x * 4 + wave_id(), cb0 = u % G * CB;
+  const int64_t row0 = (int64_t)(u / G) * 16, row = row0 + e;
+  if (row0 >= a.rows) return;
+  const bool ok = row < a.rows;
+  const int64_t src = ok ? row : row0;
+  floatx4 acc[CB];
+  if constexpr (!PHASE_C) {
+    float4 x[2 * NB];
+    tf_load<NB>(a.in0 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[0]));
+    tf_load<NB>(a.in1 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[NB]));
+    tf_gemm_cols<CB, 2 * NB, 2 * NB>(a.mlp.lin[0].wf, cb0, 0, x, acc, lane);
+    if (ok) {
+#pragma unroll
+      for (int c = 0; c < CB; ++c)
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.hid[0]) + row * L + (cb0 + c) * 16 + q * 4) =
+            tf_relu(tf_add(acc[c], rt_ld4(a.mlp.lin[0].b, cb0 + c, q)));
+    }
+  } else {
+    float4 z[NB];
+    tf_load<NB>(reinterpret_cast<const float*>(a.delta[0]) + src * L, q, z);
+    tf_gemm_cols<CB, NB, NB>(a.mlp.lin[0].wb, cb0, 0, z, acc, lane);
+    const bool agg = cb0 >= NB;
+    if (ok) {
+#pragma unroll
+      for (int c = 0; c < CB; ++c) {
+        const int cb = cb0 + c - (agg ? NB : 0);
+        float4 v = make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
+        if (!agg) v = tf_add(acc[c], rt_ld4(a.dm + row * L, cb, q));
+        *reinterpret_cast<float4*>((agg ? a.dx1 : a.dx0) + row * L + cb * 16 + q * 4) = v;
+      }
+    }
+  }
+}
+
+// Node half forward, v + LN(MLP([v | agg])).  Phase A: h_1 = relu(W_1 [v | agg]
+// + b_1); phase B: the rest.  L = 64 runs both in one launch; at L = 128 (128
+// and 64 KiB of weights) phase A leaves h_1 in the output rows, which phase B's
+// wave reads before it writes them.
+template <int L, int D, bool A, bool B>
+struct TfNodeFwdLay {
+  static constexpr int NB = L / 16, W = L * L * 4;
+  static constexpr int OFF_WH = A ? 2 * W : 0, OFF_VEC = OFF_WH + (B ? (D - 1) * W : 0);
+  static constexpr int END = OFF_VEC + 5 * L * 4;  // b_1, last bias, gamma, beta, hidden bias
+  static_assert(END <= 160 * 1024, "LDS");
+};
+template <int L, int D, bool A, bool B>
+__global__ __launch_bounds__(TF_NTH) void node_fwd_f32_kernel(RowsFwdArgs a) {
+  using Lay = TfNodeFwdLay<L, D, A, B>;
+  constexpr int NB = Lay::NB;
+  extern __shared__ __align__(16) unsigned char lds[];
+  float4* W1 = reinterpret_cast<float4*>(lds);
+  float4* WL = reinterpret_cast<float4*>(lds + Lay::OFF_WH);
+  float4* WH = reinterpret_cast<float4*>(lds + Lay::OFF_WH + Lay::W);
+  float* vb1 = reinterpret_cast<float*>(lds + Lay::OFF_VEC);
+  float *vbl = vb1 + L, *vg = vb1 + 2 * L, *vbt = vb1 + 3 * L, *vbh = vb1 + 4 * L;
+  if constexpr (A) {
+    tf_copy_frags<NB, 2 * NB, TF_NTH, 2 * NB>(W1, a.mlp.lin[0].wf, 0);
+    rt_copy_vec(vb1, a.mlp.lin[0].b, L);
+  }
+  if constexpr (B) {
+    tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
+    if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
+    rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
+    rt_copy_vec(vg, a.mlp.gamma, L);
+    rt_copy_vec(vbt, a.mlp.beta, L);
+    if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
+  }
+  __syncthreads();
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  float* out = reinterpret_cast<float*>(a.out);
+  const int64_t nt = (a.rows + 15) / 16;
+  for (int64_t t = blockIdx.x + (int64_t)gridDim.x * wave; t < nt; t += (int64_t)gridDim.x * TF_NWV) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int e = ln & 15, q = ln >> 4, slot = tf_slot(e, q);
+    const int64_t row = t * 16 + e;
+    const bool ok = row < a.rows;
+    const int64_t src = ok ? row : t * 16;
+    floatx4 acc[NB];
+    float4 h[NB], v[NB];
+    if constexpr (A) {
+      float4 x[2 * NB];
+      tf_load<NB>(a.in0 + src * L, q, v);
+      tf_load<NB>(a.in1 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[NB]));
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) x[cb] = v[cb];
+      tf_gemm<NB, 2 * NB>(W1, x, acc, slot);
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vb1, cb, q)));
+      if constexpr (!B) {
+        if (ok) tf_store<NB>(out + row * L, q, h);
+      }
+    } else {
+      tf_load<NB>(out + src * L, q, h);
+      tf_load<NB>(a.in0 + src * L, q, v);
+    }
+    if constexpr (B) {
+      if constexpr (D == 3) {
+        tf_gemm<NB>(WH, h, acc, slot);
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) h[cb] = tf_relu(tf_add(acc[cb], rt_ld4(vbh, cb, q)));
+      }
+      tf_gemm<NB>(WL, h, acc, slot);
+      float4 y[NB];
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) y[cb] = tf_add(acc[cb], rt_ld4(vbl, cb, q));
+      const float mu = rt_sum4(tf_lane_sum<NB>(y)) / L;
+      const float rs = tf_rstd<NB, L>(y, mu, a.eps);
+      if (ok) {
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb) {
+          const float4 g = rt_ld4(vg, cb, q), bt = rt_ld4(vbt, cb, q);
+          y[cb].x = (g.x * ((y[cb].x - mu) * rs) + bt.x) + v[cb].x;
+          y[cb].y = (g.y * ((y[cb].y - mu) * rs) + bt.y) + v[cb].y;
+          y[cb].z = (g.z * ((y[cb].z - mu) * rs) + bt.z) + v[cb].z;
+          y[cb].w = (g.w * ((y[cb].w - mu) * rs) + bt.w) + v[cb].w;
+        }
+        tf_store<NB>(out + row * L, q, y);
+      }
+    }
+  }
+}
+
+// The same for few rows (L = 128, depth 2): a workgroup of four waves per
+// 16-row tile, two output column blocks per wave and product, the weights read
+// straight from the packed copies; h_1 and the row sums pass through LDS.
+// 1,885 rows: 9 us a launch, against 17 for four waves on 64-row tiles.
+__global__ __launch_bounds__(256) void node_fwd_cols_kernel(RowsFwdArgs a) {
+  constexpr int L = 128, NB = 8, CB = 2, LDH = L + 4;
+  __shared__ __align__(16) float H[16 * LDH];
+  __shared__ float S[2][4][16];
+  const int wave = wave_id(), lane = threadIdx.x & 63, e = lane & 15, q = lane >> 4, cb0 = wave * CB;
+  const int64_t row0 = (int64_t)blockIdx.x * 16, row = row0 + e;
+  const bool ok = row < a.rows;
+  const int64_t src = ok ? row : row0;
+  float4 x[2 * NB], v[CB];
+  tf_load<NB>(a.in0 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[0]));
+  tf_load<NB>(a.in1 + src * L, q, reinterpret_cast<float4(&)[NB]>(x[NB]));
+  floatx4 acc[CB];
+  tf_gemm_cols<CB, 2 * NB, 2 * NB>(a.mlp.lin[0].wf, cb0, 0, x, acc, lane);
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    *reinterpret_cast<float4*>(H + e * LDH + (cb0 + c) * 16 + q * 4) =
+        tf_relu(tf_add(acc[c], rt_ld4(a.mlp.lin[0].b, cb0 + c, q)));
+    v[c] = rt_ld4(a.in0 + src * L, cb0 + c, q);
+  }
+  __syncthreads();
+  float4 h[NB];
+#pragma unroll
+  for (int kg = 0; kg < NB; ++kg) h[kg] = *reinterpret_cast<const float4*>(H + e * LDH + kg * 16 + q * 4);
+  tf_gemm_cols<CB, NB, NB>(a.mlp.lin[1].wf, cb0, 0, h, acc, lane);
+  float4 y[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) y[c] = tf_add(acc[c], rt_ld4(a.mlp.lin[1].b, cb0 + c, q));
+  const float s1 = rt_sum4(tf_lane_sum<CB>(y));
+  if (q == 0) S[0][wave][e] = s1;
+  __syncthreads();
+  const float mu = (((S[0][0][e] + S[0][1][e]) + S[0][2][e]) + S[0][3][e]) / L;
+  float4 d[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) {
+    const float4 u = make_float4(y[c].x - mu, y[c].y - mu, y[c].z - mu, y[c].w - mu);
+    d[c] = make_float4(u.x * u.x, u.y * u.y, u.z * u.z, u.w * u.w);
+  }
+  const float s2 = rt_sum4(tf_lane_sum<CB>(d));
+  if (q == 0) S[1][wave][e] = s2;
+  __syncthreads();
+  const float rs = 1.0f / sqrtf((((S[1][0][e] + S[1][1][e]) + S[1][2][e]) + S[1][3][e]) / L + a.eps);
+  if (ok) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      const float4 g = rt_ld4(a.mlp.gamma, cb0 + c, q), bt = rt_ld4(a.mlp.beta, cb0 + c, q);
+      float4 o;
+      o.x = (g.x * ((y[c].x - mu) * rs) + bt.x) + v[c].x;
+      o.y = (g.y * ((y[c].y - mu) * rs) + bt.y) + v[c].y;
+      o.z = (g.z * ((y[c].z - mu) * rs) + bt.z) + v[c].z;
+      o.w = (g.w * ((y[c].w - mu) * rs) + bt.w) + v[c].w;
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.out) + row * L + (cb0 + c) * 16 + q * 4) = o;
+    }
+  }
+}
+
 template <class F>
 void allow_lds(F* fn, int bytes) {
   if (bytes > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// Working waves per workgroup for `edges` edges: as many as give each a
-// 16-edge tile, so that a small graph's tiles are full and lie on SIMDs of
-// their own (a tile's products fill one SIMD's matrix pipe: two short tiles on
-// one SIMD take as long as two full ones).
-int tf_waves(int64_t edges) {
-  const int64_t w = (edges + 16 * RS_GRID - 1) / (16 * RS_GRID);
-  return (int)(w < 1 ? 1 : w < TF_NWV ? w : TF_NWV);
-}
+// Working waves per workgroup for `edges` edges: one per SIMD while that gives
+// every wave a single 16-edge tile (ranges are receiver-aligned, so 11 edges a
+// wave on average), else all.  On 10,900 edges a wave per full tile (three a
+// workgroup) left some waves two tiles: forward 27.8 us.
+int tf_waves(int64_t edges) { return edges <= (int64_t)4 * RS_GRID * 11 ? 4 : TF_NWV; }
 
 template <int L, int D>
 hipError_t edge_fwd_f32_t(const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st) {
@@ -961,6 +1209,12 @@ template <int L>
 hipError_t node_proj_f32_t(const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1, float* ps,
                            float* ps_halo, float* pr, hipStream_t st) {
   const int64_t tiles = (n_owned + 15) / 16 + (n_halo + 15) / 16;
+  if (tiles <= TF_COLS_TILES) {
+    const int64_t units = (2 * ((n_owned + 15) / 16) + (n_halo + 15) / 16) * (L / 32);
+    hipLaunchKernelGGL((node_proj_cols_kernel<L>), dim3((unsigned)((units + 3) / 4)), dim3(256), 0, st, V, H, n_owned,
+                       n_halo, w1, ps, ps_halo, pr);
+    return hipGetLastError();
+  }
   const int64_t g = (tiles + 7) / 8 * 16;  // both sides, multiples of 8 workgroups each
   hipLaunchKernelGGL((node_proj_f32_kernel<L>), dim3((unsigned)(g < 512 ? g : 512)), dim3(TF_NTH), L * L * 4, st, V, H,
                      n_owned, n_halo, w1, ps, ps_halo, pr);
@@ -980,6 +1234,14 @@ hipError_t enc_fwd_f32_t(const RowsFwdArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int L, int D, bool A, bool B>
+hipError_t node_fwd_f32_t(const RowsFwdArgs& a, hipStream_t st) {
+  using Lay = TfNodeFwdLay<L, D, A, B>;
+  allow_lds(node_fwd_f32_kernel<L, D, A, B>, Lay::END);
+  hipLaunchKernelGGL((node_fwd_f32_kernel<L, D, A, B>), dim3(tf_rows_grid(a.rows)), dim3(TF_NTH), Lay::END, st, a);
+  return hipGetLastError();
+}
+
 template <int L, int D, int KIND, int NKF, bool A, bool B, bool C>
 hipError_t rows_bwd_f32_t(const RowsBwdArgs& a, hipStream_t st) {
   using Lay = TfRowsLay<L, D, KIND, NKF, A, B, C>;
@@ -995,8 +1257,17 @@ hipError_t rows_bwd_f32_d(int kind, const RowsBwdArgs& a, hipStream_t st) {
     if constexpr (L == 64) {
       return rows_bwd_f32_t<L, D, NODE_BLOCK, 1, true, true, true>(a, st);
     } else {
-      hipError_t e = rows_bwd_f32_t<L, D, NODE_BLOCK, 1, true, false, false>(a, st);
+      const int64_t tiles = (a.rows + 15) / 16;
+      const bool cols = tiles > 0 && tiles <= TF_COLS_TILES;
+      if (cols)  // (phase A: L / 32 column groups of a tile, phase C: L / 16)
+        hipLaunchKernelGGL((node_bwd_cols_kernel<L, false>), dim3((unsigned)(tiles * (L / 32) / 4)), dim3(256), 0, st, a);
+      hipError_t e = cols ? hipGetLastError() : rows_bwd_f32_t<L, D, NODE_BLOCK, 1, true, false, false>(a, st);
       if (e == hipSuccess) e = rows_bwd_f32_t<L, D, NODE_BLOCK, 1, false, true, false>(a, st);
+      if (e != hipSuccess) return e;
+      if (cols) {
+        hipLaunchKernelGGL((node_bwd_cols_kernel<L, true>), dim3((unsigned)(tiles * (L / 16) / 4)), dim3(256), 0, st, a);
+        return hipGetLastError();
+      }
       if (e == hipSuccess) e = rows_bwd_f32_t<L, D, NODE_BLOCK, 1, false, false, true>(a, st);
       return e;
     }
@@ -1012,16 +1283,27 @@ bool rows_f32(int prec, int L, int D, int kind, int fin) {
   if (prec != F32 || (L != 64 && L != 128)) return false;
   return kind == NODE_BLOCK || ((kind == ENC_NODE || kind == ENC_EDGE) && fin <= 16);
 }
-// (128, 3) keeps the other forward, as its edge half does: one pass per step
-// beside a streaming edge forward of many times its work.
-bool enc_fwd_f32(int prec, int L, int D, int kind, int fin) {
-  return kind != NODE_BLOCK && rows_f32(prec, L, D, kind, fin) && edge_f32(prec, L, D);
+// (128, 3) keeps the other forward kernels, as its edge half does, which takes
+// many times their work.
+bool rows_fwd_f32(int prec, int L, int D, int kind, int fin) {
+  return rows_f32(prec, L, D, kind, fin) && edge_f32(prec, L, D);
 }
 int rows_f32_grid(int64_t rows) { return tf_rows_grid(rows); }
 int rows_f32_w1_parts(int64_t rows, int kind, int fin) { return kind == ENC_EDGE && fin <= 4 ? tf_rows_grid(rows) : 0; }
 
-hipError_t launch_enc_fwd_f32(int L, int D, const RowsFwdArgs& a, hipStream_t st) {
+hipError_t launch_rows_fwd_f32(int L, int D, int kind, const RowsFwdArgs& a, hipStream_t st) {
   if (a.rows == 0) return hipSuccess;
+  if (kind == NODE_BLOCK) {
+    if (L == 64) return D == 2 ? node_fwd_f32_t<64, 2, true, true>(a, st) : node_fwd_f32_t<64, 3, true, true>(a, st);
+    if (L != 128 || D != 2) return hipErrorInvalidValue;
+    const int64_t tiles = (a.rows + 15) / 16;
+    if (tiles <= TF_COLS_TILES) {
+      hipLaunchKernelGGL(node_fwd_cols_kernel, dim3((unsigned)tiles), dim3(256), 0, st, a);
+      return hipGetLastError();
+    }
+    const hipError_t e = node_fwd_f32_t<128, 2, true, false>(a, st);
+    return e == hipSuccess ? node_fwd_f32_t<128, 2, false, true>(a, st) : e;
+  }
   if (L == 64) return D == 2 ? enc_fwd_f32_t<64, 2, 1>(a, st) : enc_fwd_f32_t<64, 3, 1>(a, st);
   if (L == 128 && D == 2) return enc_fwd_f32_t<128, 2, 1>(a, st);
   return hipErrorInvalidValue;

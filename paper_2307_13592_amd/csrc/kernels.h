@@ -234,14 +234,14 @@ bool edge_f32(int prec, int L, int D);
 hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st);
 hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st);
 // fp32 row kernels in T form: encoders of at most 16 features and the node
-// half's backward, latent 64 or 128.  The edge encoder's backward forms the
+// half, latent 64 or 128 (forward: not 128 at depth 3).  The edge encoder's backward forms the
 // first Linear's weight gradient itself for at most 4 features (w1_part, that
 // many partials; 0: it stores delta[0]).
 bool rows_f32(int prec, int L, int D, int kind, int fin);
-bool enc_fwd_f32(int prec, int L, int D, int kind, int fin);
+bool rows_fwd_f32(int prec, int L, int D, int kind, int fin);
 int rows_f32_grid(int64_t rows);
 int rows_f32_w1_parts(int64_t rows, int kind, int fin);
-hipError_t launch_enc_fwd_f32(int L, int D, const RowsFwdArgs& a, hipStream_t st);
+hipError_t launch_rows_fwd_f32(int L, int D, int kind, const RowsFwdArgs& a, hipStream_t st);
 hipError_t launch_rows_bwd_f32(int L, int D, int kind, const RowsBwdArgs& a, hipStream_t st);
 hipError_t launch_node_proj_f32(int L, const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1,
                                 float* ps, float* ps_halo, float* pr, hipStream_t st);

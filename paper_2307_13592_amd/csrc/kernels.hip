@@ -5821,7 +5821,7 @@ int rows_rt_w1_parts(int prec, int L, int D, int kind, int fin, int64_t rows) {
 }
 
 hipError_t launch_rows_fwd(int prec, int L, int D, int kind, const RowsFwdArgs& a, hipStream_t st) {
-  if (enc_fwd_f32(prec, L, D, kind, a.fin)) return launch_enc_fwd_f32(L, D, a, st);
+  if (rows_fwd_f32(prec, L, D, kind, a.fin)) return launch_rows_fwd_f32(L, D, kind, a, st);
   if (rows_rw(prec, L, D, kind)) {
     if (kind == ENC_EDGE) return D == 2 ? rows_rw_enc_fwd_t<2>(a, st) : rows_rw_enc_fwd_t<3>(a, st);
     return D == 2 ? rows_rw_fwd_t<2>(a, st) : rows_rw_fwd_t<3>(a, st);
@@ -5841,7 +5841,10 @@ hipError_t launch_rows_fwd(int prec, int L, int D, int kind, const RowsFwdArgs& 
     switch (kind) {                                                                         \
       case ENC_NODE: return rows_fwd_t<PP, LL, DD, ENC_NODE>(a, st);                        \
       case ENC_EDGE: return rows_fwd_t<PP, LL, DD, ENC_EDGE>(a, st);                        \
-      case NODE_BLOCK: return rows_fwd_t<PP, LL, DD, NODE_BLOCK>(a, st);                    \
+      case NODE_BLOCK:                                                                      \
+        if constexpr (PP == F32 && (LL == 64 || (LL == 128 && DD == 2)))                    \
+          return hipErrorInvalidValue; /* rows_fwd_f32 */                                   \
+        else return rows_fwd_t<PP, LL, DD, NODE_BLOCK>(a, st);                              \
       default: return rows_fwd_t<PP, LL, DD, DECODER>(a, st);                               \
     }                                                                                       \
   }
