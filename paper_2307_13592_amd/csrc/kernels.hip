@@ -5296,6 +5296,40 @@ __global__ __launch_bounds__(NT) void sender_range_kernel(const int32_t* __restr
 constexpr int DWS_NT = 256;
 constexpr int DWS_GRID = 256;
 constexpr int DWS_WAVES = DWS_GRID * DWS_NT / 64;
+constexpr int DWS_LDS = 2 * 65536;  // two waves' 128 x 128 tiles, on their way to the other two
+
+// Adds the tiles of a workgroup's four waves into wave 0's ((0 + 2) + (1 +
+// 3)), two at a time through LDS; true for wave 0.  One partial per workgroup
+// instead of one per wave: 16 MiB written and read back instead of 64, as
+// much as the operands of 65,000 bf16 rows.
+__device__ __forceinline__ bool dws_combine(floatx4 (&acc)[8][8], float4* lds, int wv, int lane) {
+  auto put = [&](float4* d) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj)
+        d[(j * 8 + jj) * 64 + lane] = make_float4(acc[j][jj][0], acc[j][jj][1], acc[j][jj][2], acc[j][jj][3]);
+  };
+  auto add = [&](const float4* d) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj) {
+        const float4 v = d[(j * 8 + jj) * 64 + lane];
+        acc[j][jj][0] += v.x;
+        acc[j][jj][1] += v.y;
+        acc[j][jj][2] += v.z;
+        acc[j][jj][3] += v.w;
+      }
+  };
+  if (wv >= 2) put(lds + (wv - 2) * 4096);
+  __syncthreads();
+  if (wv < 2) add(lds + wv * 4096);
+  if (wv == 1) put(lds + 4096);
+  __syncthreads();
+  if (wv == 0) add(lds + 4096);
+  return wv == 0;
+}
 
 // v[r][k]: row r, columns 2k (low half) and 2k + 1 -> f[c][p]: column c, rows
 // 2p (low half) and 2p + 1.
@@ -5374,7 +5408,7 @@ __device__ __forceinline__ void dws_split(const float4 (&v)[8][2], uint32_t (&hi
   }
 }
 
-// part[w] (16384 floats, accumulator order [j][j'][lane][4]) = wave w's sum.
+// part[b] (16384 floats, accumulator order [j][j'][lane][4]) = workgroup b's sum.
 // SPLIT: D is fp32 and enters the products as hi + lo (two MFMAs each).
 // AF32: A is fp32, rounded to bf16 as it is loaded.
 // QUAD: a 256 x 256 product.  The four waves of a workgroup take the same rows
@@ -5445,8 +5479,12 @@ __global__ __launch_bounds__(DWS_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) 
       dws_mma(fd, fa, acc);
     }
   }
+  if constexpr (!QUAD) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    if (!dws_combine(acc, reinterpret_cast<float4*>(lds), wv, lane)) return;
+  }
   float4* out =
-      reinterpret_cast<float4*>(part + (QUAD ? (int64_t)wv * gridDim.x + blockIdx.x : w) * 16384);
+      reinterpret_cast<float4*>(part + (QUAD ? (int64_t)wv * gridDim.x + blockIdx.x : (int64_t)blockIdx.x) * 16384);
 #pragma unroll
   for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -5463,7 +5501,7 @@ __global__ __launch_bounds__(DWS_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 // half h stands for column 64 h + 4 m + c; accumulator block (h, c, h', c')
 // then holds dW[64 h + 4 i + c][64 h' + 4 j + c'] at (i, j) of its 16 x 16
 // tile.  One wave per SIMD, 64 blocks = the 256 accumulator registers; a
-// 16-row step's loads are issued one step ahead.  part[w] = wave w's sum in
+// 16-row step's loads are issued one step ahead.  part[b] = workgroup b's sum in
 // plain [o][i] order (reduced by dw_reduce_kernel).
 __device__ __forceinline__ void dwf_load(const float* __restrict__ D, int ldd, const float* __restrict__ A, int lda,
                                          int64_t row, int64_t R, int m, float4 (&v)[4][4]) {
@@ -5514,7 +5552,9 @@ __global__ __launch_bounds__(DWS_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) 
               acc[h * 4 + c][hh * 4 + cc] = __builtin_amdgcn_mfma_f32_16x16x4f32(
                   f4c(cur[g][h], c), f4c(cur[g][2 + hh], cc), acc[h * 4 + c][hh * 4 + cc], 0, 0, 0);
   }
-  float* out = part + w * 16384;
+  extern __shared__ __align__(16) unsigned char lds[];
+  if (!dws_combine(acc, reinterpret_cast<float4*>(lds), wave_id(), lane)) return;
+  float* out = part + (int64_t)blockIdx.x * 16384;
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -6135,8 +6175,8 @@ hipError_t launch_sender_range(const int32_t* send, int64_t e_lo, int64_t e_hi, 
   hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, range + 1, (int64_t)1, (int32_t)-1);
   const int64_t n = e_hi - e_lo;
   if (n > 0) {
-    int64_t grid = (n + NT - 1) / NT;
-    if (grid > 1024) grid = 1024;
+    int64_t grid = (n + 4 * NT - 1) / (4 * NT);
+    if (grid > 512) grid = 512;
     hipLaunchKernelGGL(sender_range_kernel, dim3((unsigned)grid), dim3(NT), 0, st, send, e_lo, e_hi, range);
   }
   return hipGetLastError();
@@ -6163,12 +6203,13 @@ bool dw_stream_f32_ok(int prec, const DwArgs& a) {
 }
 
 hipError_t launch_dw_stream_f32(const DwArgs& a, float* dst, int ldw, int accumulate, hipStream_t st) {
-  hipLaunchKernelGGL(dw_stream_f32_kernel, dim3(DWS_GRID), dim3(DWS_NT), 0, st,
+  allow_lds(dw_stream_f32_kernel, DWS_LDS);
+  hipLaunchKernelGGL(dw_stream_f32_kernel, dim3(DWS_GRID), dim3(DWS_NT), DWS_LDS, st,
                      reinterpret_cast<const float*>(a.delta), a.ldd, reinterpret_cast<const float*>(a.a0), a.lda0,
                      a.R, a.part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_dw_reduce(a.part, DWS_WAVES, 128, 128, dst, ldw, accumulate, st);
+  return launch_dw_reduce(a.part, DWS_GRID, 128, 128, dst, ldw, accumulate, st);
 }
 
 bool dw_stream_ok(int prec, const DwArgs& a) {
@@ -6179,18 +6220,16 @@ bool dw_stream_ok(int prec, const DwArgs& a) {
 }
 
 hipError_t launch_dw_stream(const DwArgs& a, float* dst, int ldw, int accumulate, hipStream_t st) {
-  if (a.d_kind == 1)
-    hipLaunchKernelGGL((dw_stream_kernel<true, false>), dim3(DWS_GRID), dim3(DWS_NT), 0, st, a.delta, a.ldd, a.a0,
-                       a.lda0, a.R, a.part);
-  else if (a.a_kind == 1)
-    hipLaunchKernelGGL((dw_stream_kernel<false, true>), dim3(DWS_GRID), dim3(DWS_NT), 0, st, a.delta, a.ldd, a.a0,
-                       a.lda0, a.R, a.part);
-  else
-    hipLaunchKernelGGL((dw_stream_kernel<false, false>), dim3(DWS_GRID), dim3(DWS_NT), 0, st, a.delta, a.ldd, a.a0,
-                       a.lda0, a.R, a.part);
-  hipError_t e = hipGetLastError();
+  auto run = [&](auto* k) {
+    allow_lds(k, DWS_LDS);
+    hipLaunchKernelGGL(k, dim3(DWS_GRID), dim3(DWS_NT), DWS_LDS, st, a.delta, a.ldd, a.a0, a.lda0, a.R, a.part);
+    return hipGetLastError();
+  };
+  const hipError_t e = a.d_kind == 1   ? run(dw_stream_kernel<true, false>)
+                       : a.a_kind == 1 ? run(dw_stream_kernel<false, true>)
+                                       : run(dw_stream_kernel<false, false>);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(dw_stream_reduce_kernel, dim3(16384 / 64), dim3(NT), 0, st, a.part, DWS_WAVES, dst, ldw,
+  hipLaunchKernelGGL(dw_stream_reduce_kernel, dim3(16384 / 64), dim3(NT), 0, st, a.part, DWS_GRID, dst, ldw,
                      accumulate);
   return hipGetLastError();
 }
