@@ -323,7 +323,7 @@ WsPlan make_plan(const mgn_model* m, const mgn_graph* g) {
   // bias / LayerNorm partials of a row kernel and of an edge kernel
   p.vstride = (size_t)BWD_GRID * nvec;
   p.VPART = take(4 * 2 * p.vstride);
-  p.SRANGE = take(8);  // sender-id range of a backward edge chunk
+  p.SRANGE = take(8 * (p.cr.size() - 1));  // sender-id range of each backward edge chunk
   p.total = o;
   return p;
 }
@@ -975,7 +975,11 @@ struct Bwd {
 
   // DecNode: dL/dv^K into DV[0]
   mgn_status decoder(const float* d_out) {
-    hipError_t e;
+    hipError_t e = hipSuccess;
+    // the edge chunks' sender ranges, the same for every block
+    for (size_t c = 0; nch > 1 && e == hipSuccess && c < nch; ++c)
+      e = launch_sender_range(g->send, p.ce[c], p.ce[c + 1], (int32_t*)(ws + p.SRANGE) + 2 * c, st);
+    CHK("sender ranges");
     const MlpL& ml = m->dec();
     RowsBwdArgs a = rows_args(ml, no, DEL_N, HID_N);
     a.in0 = b.V(K);
@@ -1157,9 +1161,8 @@ struct Bwd {
           // per-sender sums of dz_0, chunk by chunk in ascending edge order:
           // zero once, then each chunk adds to the senders of its edges only
           Timed t_(m, MGN_T_INPUT_GRAD, st);
-          int32_t* sr = (int32_t*)(ws + p.SRANGE);
+          const int32_t* sr = (const int32_t*)(ws + p.SRANGE) + 2 * c;
           if (c == 0) e = launch_zero(DZS, (no + nh) * (int64_t)L, st);
-          if (e == hipSuccess) e = launch_sender_range(g->send, e0, e0 + rows, sr, st);
           if (e == hipSuccess)
             e = launch_sender_sums(m->prec, L, g->trow_ptr, g->tedge, DEL_E[0], e0, e0 + rows, no + nh, DZS, 0, sr,
                                    st);

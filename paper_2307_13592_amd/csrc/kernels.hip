@@ -5262,9 +5262,11 @@ __global__ __launch_bounds__(NT) void sender_sums_kernel(const int32_t* __restri
 
 // range[0] = min, range[1] = max of send[e_lo .. e_hi) (range pre-filled
 // with INT32_MAX, -1); integer minimum and maximum, so the result does not
-// depend on the order of the updates.
+// depend on the order of the updates.  One update per workgroup: with one per
+// wave, 8,192 atomics on two words took 95 us.
 __global__ __launch_bounds__(NT) void sender_range_kernel(const int32_t* __restrict__ send, int64_t e_lo, int64_t e_hi,
                                                           int32_t* __restrict__ range) {
+  __shared__ int32_t slo[NW], shi[NW];
   int32_t lo = INT32_MAX, hi = -1;
   for (int64_t e = e_lo + (int64_t)blockIdx.x * NT + threadIdx.x; e < e_hi; e += (int64_t)gridDim.x * NT) {
     const int32_t v = send[e];
@@ -5276,9 +5278,20 @@ __global__ __launch_bounds__(NT) void sender_range_kernel(const int32_t* __restr
     lo = a < lo ? a : lo;
     hi = b > hi ? b : hi;
   }
-  if ((threadIdx.x & 63) == 0 && hi >= 0) {
-    atomicMin(range, lo);
-    atomicMax(range + 1, hi);
+  if ((threadIdx.x & 63) == 0) {
+    slo[threadIdx.x >> 6] = lo;
+    shi[threadIdx.x >> 6] = hi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NW; ++w) {
+      lo = slo[w] < lo ? slo[w] : lo;
+      hi = shi[w] > hi ? shi[w] : hi;
+    }
+    if (hi >= 0) {
+      atomicMin(range, lo);
+      atomicMax(range + 1, hi);
+    }
   }
 }
 
