@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmgn.so")
-SOURCES = ["kernels.hip", "f32_kernels.hip", "dw.hip", "api.cpp", "graph_host.cpp", "noalloc.hip"]
+SOURCES = ["kernels.hip", "f32_kernels.hip", "dw.hip", "wide.hip", "api.cpp", "graph_host.cpp", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -1136,7 +1136,9 @@ struct Bwd {
         a.e_base = e0;
         {
           Timed t_(m, MGN_T_EDGE_BWD, st);
-          e = p.f32 ? launch_edge_bwd_f32(L, D, a, rows, st) : launch_edge_bwd(m->prec, L, D, a, BWD_GRID, st);
+          e = p.f32 ? launch_edge_bwd_f32(L, D, a, rows, st)
+              : edge_wide(m->prec, L, D, rows) ? launch_edge_bwd_wide(D, a, rows, st)
+                                               : launch_edge_bwd(m->prec, L, D, a, BWD_GRID, st);
         }
         CHK("edge block");
         e = run_vec(ml, VPE, acc, edge_bwd_grid(m->prec, L, D, BWD_GRID));

@@ -250,6 +250,14 @@ hipError_t launch_node_proj(int L, const void* v16, int64_t n_local, const Lin& 
 // weights streamed through LDS (the forward, and a backward that recomputes
 // h_1, need the node projections of launch_node_proj for the block).
 bool edge_rsb(int prec, int L, int D);
+// bf16, l = 256, from WIDE_ROWS rows on: the backward of the edge half, the
+// node half and the encoders as one launch per Linear (wide.hip).  The edge
+// encoder then stores delta[0].
+constexpr int64_t WIDE_ROWS = 32768;
+bool edge_wide(int prec, int L, int D, int64_t edges);
+hipError_t launch_edge_bwd_wide(int D, const EdgeBwdArgs& a, int64_t rows, hipStream_t st);
+bool rows_wide(int prec, int L, int D, int kind, int64_t rows);
+hipError_t launch_rows_bwd_wide(int D, int kind, const RowsBwdArgs& a, hipStream_t st);
 hipError_t launch_input_grad(int prec, int L, const InGradArgs& a, hipStream_t st);
 // Per-sender sums of dz_0 over the edges [e_lo, e_hi) (dz rows stored from e_lo),
 // assigned (first) or added into dzs.

@@ -1597,14 +1597,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(EdgeWpe<L>::
 constexpr int RS_NWV = 8;              // waves per workgroup
 constexpr int RS_NTH = 64 * RS_NWV;
 
-// bf16 / fp32 element index of (row, col) in a 16-row scratch tile of width
-// L whose 16-byte chunks are XOR-swizzled by row (conflict-free both for
-// accumulator-order writes and for fragment / row-order reads).
-template <int L>
-__device__ __forceinline__ int rs_sw16(int row, int col) {
-  constexpr int M = (L / 8 < 16 ? L / 8 : 16) - 1;
-  return row * L + ((((col >> 3) ^ (row & M))) << 3) + (col & 7);
-}
 // acc[cb] = sum over k-groups of A[kg] x B[cb][kg]: one 16-row tile, every
 // 16-column block cb, B fragments in LDS ([cb][kg][lane], 16 bytes each).
 template <int NB, int NKG>
@@ -1615,17 +1607,6 @@ __device__ __forceinline__ void rs_gemm(const uint4 (&A)[NKG], const uint4* Bl, 
   for (int kg = 0; kg < NKG; ++kg)
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb) PBF16::mma(acc[cb], A[kg], Bl[(cb * NKG + kg) * 64 + lane]);
-}
-
-// Copies nb 16-column blocks x nkg k-groups of packed fragments (source
-// block stride src_nkg k-groups, first k-group kg0) into LDS, all threads.
-__device__ __forceinline__ void rs_copy_frags(uint4* dst, const uint4* __restrict__ src, int nb, int nkg, int src_nkg,
-                                              int kg0) {
-  const int total = nb * nkg * 64;
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    const int cb = i / (nkg * 64), kg = (i / 64) % nkg, ln = i % 64;
-    dst[i] = src[((size_t)cb * src_nkg + kg0 + kg) * 64 + ln];
-  }
 }
 
 // ----------------------------------------------------------------- T form ---
@@ -1643,120 +1624,6 @@ __device__ __forceinline__ void rs_copy_frags(uint4* dst, const uint4* __restric
 // instructions).  Column sums over a tile's rows are a reduce-scatter across
 // the 16 lanes of a group (DPP).  Rows in memory keep the plain column order:
 // a lane reads or writes 4 consecutive columns per 16-column block.
-
-// Like rs_copy_frags, with the eight k-slots of every fragment reordered so
-// that slot j of lane group q pairs with k = 32 kg + 16 (j / 4) + 4 q + j % 4:
-// its low half comes from lane group q / 2, its high half from 2 + q / 2,
-// slots 4 (q % 2) .. of each.
-__device__ __forceinline__ void rt_copy_frags(uint4* dst, const uint4* __restrict__ src, int nb, int nkg, int src_nkg,
-                                              int kg0) {
-  const int total = nb * nkg * 64;
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    const int cb = i / (nkg * 64), kg = (i / 64) % nkg, ln = i % 64, q = ln >> 4, c = ln & 15;
-    const uint2* s = reinterpret_cast<const uint2*>(src + ((size_t)cb * src_nkg + kg0 + kg) * 64);
-    const uint2 lo = s[(c + 16 * (q >> 1)) * 2 + (q & 1)];
-    const uint2 hi = s[(c + 16 * (2 + (q >> 1))) * 2 + (q & 1)];
-    dst[i] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-  }
-}
-
-// acc[cb] = sum over k-groups of W[cb][kg] (LDS, [cb][kg][lane]) x X[kg].
-template <int NB, int NKG>
-__device__ __forceinline__ void rt_gemm(const uint4* Wl, const uint4 (&X)[NKG], floatx4 (&acc)[NB], int lane) {
-#pragma unroll
-  for (int cb = 0; cb < NB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int kg = 0; kg < NKG; ++kg)
-#pragma unroll
-    for (int cb = 0; cb < NB; ++cb) PBF16::mma(acc[cb], Wl[(cb * NKG + kg) * 64 + lane], X[kg]);
-}
-
-// Two fp32 values -> two bf16 (round to nearest even, one conversion instruction).
-__device__ __forceinline__ uint32_t bf_pack(float lo, float hi) {
-  typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-  typedef float f32x2_t __attribute__((ext_vector_type(2)));
-  const f32x2_t f = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
-}
-
-// Accumulator-order values -> bf16 B operands of the next product.
-template <int NB>
-__device__ __forceinline__ void rt_frags(const float (&v)[NB][4], uint4 (&f)[NB / 2]) {
-#pragma unroll
-  for (int kg = 0; kg < NB / 2; ++kg)
-    f[kg] = make_uint4(bf_pack(v[2 * kg][0], v[2 * kg][1]), bf_pack(v[2 * kg][2], v[2 * kg][3]),
-                       bf_pack(v[2 * kg + 1][0], v[2 * kg + 1][1]), bf_pack(v[2 * kg + 1][2], v[2 * kg + 1][3]));
-}
-
-// T-order bf16 of one k-group -> plain order.  In: lane group q holds
-// columns 32 kg + 4 q .. +3 (x, y) and 32 kg + 16 + 4 q .. +3 (z, w).  Out:
-// columns 32 kg + 8 q .. +7, one 16-byte row chunk.  A lane swap between the
-// group pairs (0, 1) <-> (2, 3), then one between groups 0 <-> 1 and 2 <-> 3.
-__device__ __forceinline__ uint4 rt_to_plain(const uint4 f) {
-  const auto s0 = __builtin_amdgcn_permlane32_swap(f.x, f.z, false, false);
-  const auto s1 = __builtin_amdgcn_permlane32_swap(f.y, f.w, false, false);
-  const auto t0 = __builtin_amdgcn_permlane16_swap(s0[0], s0[1], false, false);
-  const auto t1 = __builtin_amdgcn_permlane16_swap(s1[0], s1[1], false, false);
-  return make_uint4(t0[0], t1[0], t0[1], t1[1]);
-}
-// Inverse of rt_to_plain (both swaps are involutions, applied in reverse).
-__device__ __forceinline__ uint4 rt_from_plain(const uint4 p) {
-  const auto t0 = __builtin_amdgcn_permlane16_swap(p.x, p.z, false, false);
-  const auto t1 = __builtin_amdgcn_permlane16_swap(p.y, p.w, false, false);
-  const auto s0 = __builtin_amdgcn_permlane32_swap(t0[0], t0[1], false, false);
-  const auto s1 = __builtin_amdgcn_permlane32_swap(t1[0], t1[1], false, false);
-  return make_uint4(s0[0], s1[0], s0[1], s1[1]);
-}
-
-// The values of rt_frags -> one plain-order bf16 row, 16 bytes per lane and
-// k-group.  All lanes take part in the swaps; only lanes with ok store.
-// A stored bf16 ReLU output row as read (plain order: lane (e, q) holds its
-// row's k-slots kg * 32 + 8 q ..) -> T-order fragments, and the ReLU mask
-// their signs give: bit cb * 4 + r is set where the value is positive.
-// rt_load_relu reads the row as well.
-template <int NKH>
-__device__ __forceinline__ void rt_relu_frags(const uint4 (&raw)[NKH], uint4 (&hf)[NKH], uint32_t& mask) {
-#pragma unroll
-  for (int kg = 0; kg < NKH; ++kg) {
-    hf[kg] = rt_from_plain(raw[kg]);
-    const uint32_t w[4] = {hf[kg].x, hf[kg].y, hf[kg].z, hf[kg].w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {  // dword i: block 2 kg + i / 2, rows r = 2 (i % 2) .. + 1
-      const int cb = 2 * kg + i / 2, r = 2 * (i % 2);
-      mask |= ((w[i] & 0x7fffu) != 0u && !(w[i] & 0x8000u) ? 1u : 0u) << (cb * 4 + r);
-      mask |= (((w[i] >> 16) & 0x7fffu) != 0u && !(w[i] & 0x80000000u) ? 1u : 0u) << (cb * 4 + r + 1);
-    }
-  }
-}
-// Whether the value of T-order fragments hf at accumulator position
-// (cb, r) is positive: bf16 bits with the sign clear and a nonzero
-// magnitude, the test rt_relu_frags makes for its mask bit cb * 4 + r.
-template <int NKH>
-__device__ __forceinline__ bool rt_relu_on(const uint4 (&hf)[NKH], int cb, int r) {
-  const uint4 f = hf[cb / 2];
-  const int i = 2 * (cb % 2) + r / 2;
-  const uint32_t w = i == 0 ? f.x : i == 1 ? f.y : i == 2 ? f.z : f.w;
-  return (int32_t)(r % 2 ? (w & 0xffff0000u) : (w << 16)) > 0;
-}
-template <int NKH>
-__device__ __forceinline__ void rt_load_relu(const uint16_t* __restrict__ hp, int q, uint4 (&hf)[NKH],
-                                             uint32_t& mask) {
-  uint4 raw[NKH];
-#pragma unroll
-  for (int kg = 0; kg < NKH; ++kg) raw[kg] = *reinterpret_cast<const uint4*>(hp + kg * 32 + q * 8);
-  rt_relu_frags<NKH>(raw, hf, mask);
-}
-
-template <int NKH>
-__device__ __forceinline__ void rt_store_frags(uint16_t* __restrict__ row, int q, const uint4 (&f)[NKH], bool ok) {
-  uint4 p[NKH];
-#pragma unroll
-  for (int kg = 0; kg < NKH; ++kg) p[kg] = rt_to_plain(f[kg]);
-  if (ok) {
-#pragma unroll
-    for (int kg = 0; kg < NKH; ++kg) *reinterpret_cast<uint4*>(row + kg * 32 + q * 8) = p[kg];
-  }
-}
 
 // z_1 of a tile in T order: W_e e (MFMA) + P_s[s] + P_r[r], added in that
 // order, with b_1 inside P_r (the forward and the recompute in the backward
@@ -2537,19 +2404,6 @@ __device__ __forceinline__ void rw_gemm(int C, const uint4* buf, const uint4 (&X
   }
 }
 
-// bf16 plain-order 16-byte chunk (8 columns) -> its T-order values: cb 2 kg
-// gets .x/.y, cb 2 kg + 1 gets .z/.w (columns 4 q + r of each block).
-__device__ __forceinline__ void rw_unpack(const uint4 p, float (&lo)[4], float (&hi)[4]) {
-  const uint4 t = rt_from_plain(p);
-  lo[0] = __uint_as_float(t.x << 16);
-  lo[1] = __uint_as_float(t.x & 0xffff0000u);
-  lo[2] = __uint_as_float(t.y << 16);
-  lo[3] = __uint_as_float(t.y & 0xffff0000u);
-  hi[0] = __uint_as_float(t.z << 16);
-  hi[1] = __uint_as_float(t.z & 0xffff0000u);
-  hi[2] = __uint_as_float(t.w << 16);
-  hi[3] = __uint_as_float(t.w & 0xffff0000u);
-}
 
 // Largest tile count over the workgroup's waves (every wave must take part
 // in every chunk step of the stream).
@@ -5918,7 +5772,7 @@ static_assert((int64_t)RS_GRID * RtRowsLay<128, ENC_EDGE>::NWV * 128 * RtRowsLay
                   (int64_t)DWS_WAVES * 16384,
               "w1 partials");
 int rows_rt_w1_parts(int prec, int L, int D, int kind, int fin, int64_t rows) {
-  if (kind != ENC_EDGE || fin < 1) return 0;
+  if (kind != ENC_EDGE || fin < 1 || rows_wide(prec, L, D, kind, rows)) return 0;
   if (rows_f32(prec, L, D, kind, fin)) return rows_f32_w1_parts(rows, kind, fin);
   if (rows_rw(prec, L, D, kind)) return fin <= RW_ENC_FIN ? RS_GRID * RwEncBwdLay<3>::NWV : 0;
   if (!rows_rt(prec, L, D, kind) || fin > RtRowsLay<128, ENC_EDGE>::W1_FIN) return 0;
@@ -5981,6 +5835,7 @@ static int rows_bwd_tile(int kind) {
 
 int rows_bwd_grid(int prec, int L, int D, int kind, int fin, int64_t rows, int grid) {
   if (rows_f32(prec, L, D, kind, fin)) return rows_f32_grid(rows);
+  if (rows_wide(prec, L, D, kind, rows)) return RS_GRID;
   if (rows_rs(prec, L, D, kind) || rows_rt_bwd(prec, L, D, kind, false) || rows_rw(prec, L, D, kind)) return RS_GRID;
   int tm = 16;
 #define RG(PP, LL, DD) \
@@ -6002,6 +5857,7 @@ static hipError_t rows_bwd_rs_t(const RowsBwdArgs& a, hipStream_t st) {
 
 hipError_t launch_rows_bwd(int prec, int L, int D, int kind, const RowsBwdArgs& a, int grid, hipStream_t st) {
   if (rows_f32(prec, L, D, kind, a.fin)) return launch_rows_bwd_f32(L, D, kind, a, st);
+  if (rows_wide(prec, L, D, kind, a.rows)) return launch_rows_bwd_wide(D, kind, a, st);
   if (rows_rw(prec, L, D, kind)) {
     if (kind == ENC_EDGE) return D == 2 ? rows_rw_enc_bwd_t<2>(a, st) : rows_rw_enc_bwd_t<3>(a, st);
     return D == 2 ? rows_rw_bwd_t<2>(a, st) : rows_rw_bwd_t<3>(a, st);
