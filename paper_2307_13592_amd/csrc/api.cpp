@@ -593,9 +593,10 @@ float* proj_block(const WsPlan& p, char* ws, int k, int64_t nl, int L) {
 
 // The edge half of block k forward: node projections (row-split path), then
 // the fused edge kernel: e^{k+1} = e^k + m into eout (may equal ein, or be
-// null), ordered receiver sums into agg.
+// null), ordered receiver sums into agg.  bwd_proj: a backward will recompute
+// h_1 from the projections stored here.
 hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p, char* ws, const float* halo, int k,
-                              float* v, void* v16, const void* ein, void* eout, float* agg, hipStream_t st) {
+                              float* v, void* v16, const void* ein, void* eout, float* agg, bool bwd_proj, hipStream_t st) {
   const int64_t no = g.n_owned, nh = g.n_halo;
   const int L = m->L, D = m->D;
   if (no == 0) return hipSuccess;
@@ -621,7 +622,10 @@ hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p,
   hipError_t e = hipSuccess;
   if (rs) {
     Timed t_(m, MGN_T_NODE_PROJ, st);
-    e = launch_node_proj(L, v16, no + nh, ea.mlp.lin[0], proj, st);
+    // the row-split forward forms the sender half itself; it is stored only
+    // for a backward that recomputes h_1
+    if (edge_rs(m->prec, L, D) && !bwd_proj) e = launch_node_proj_r(L, v16, no, ea.mlp.lin[0], proj, st);
+    else e = launch_node_proj(L, v16, no + nh, ea.mlp.lin[0], proj, st);
     if (e != hipSuccess) return e;
   }
   if (p.f32) {
@@ -766,7 +770,7 @@ mgn_status fwd_block(mgn_model* m, hipStream_t st, const char* fn) {
     if (e != hipSuccess) return hip_fail(m, e, (f + " halo copy").c_str());
   }
   e = edge_forward_block(m, m->g, b.p, b.ws, m->halo, k, b.V(k), b.V16(k), b.ES(k), k + 1 < K ? b.ES(k + 1) : nullptr,
-                         b.AGG(k), st);
+                         b.AGG(k), !b.p.infer && !b.p.lean && k < b.p.h1_first, st);
   if (e != hipSuccess) return hip_fail(m, e, (f + " edge block").c_str());
   RowsFwdArgs na{};
   na.mlp = dev_mlp(m, m->node(k));
@@ -1023,7 +1027,8 @@ struct Bwd {
       // forward runs once more for it.
       const int b0 = k - k % p.s;
       for (int j = b0; j < k; ++j) {
-        e = edge_forward_block(m, *g, p, ws, m->halo, j, b.V(j), b.V16(j), b.ES(j), b.ES(j + 1), b.AGG(k - 1), st);
+        e = edge_forward_block(m, *g, p, ws, m->halo, j, b.V(j), b.V16(j), b.ES(j), b.ES(j + 1), b.AGG(k - 1), false,
+                               st);
         CHK("edge-stream recompute");
       }
       // the last block's aggregate is still where the forward left it
@@ -1031,7 +1036,7 @@ struct Bwd {
       const bool have_agg = k + 1 < K ? (k + 1) % p.s != 0 : m->agg_last;
       m->agg_last = false;
       if (!have_agg) {
-        e = edge_forward_block(m, *g, p, ws, m->halo, k, b.V(k), b.V16(k), b.ES(k), nullptr, b.AGG(k), st);
+        e = edge_forward_block(m, *g, p, ws, m->halo, k, b.V(k), b.V16(k), b.ES(k), nullptr, b.AGG(k), true, st);
         CHK("aggregate recompute");
       } else if ((edge_rs(m->prec, L, D) || edge_rsb(m->prec, L, D)) && no > 0) {
         // block k's node projections for its edge backward (the slot holds block k-1's)

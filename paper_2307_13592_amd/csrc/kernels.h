@@ -246,6 +246,9 @@ hipError_t launch_rows_bwd_f32(int L, int D, int kind, const RowsBwdArgs& a, hip
 hipError_t launch_node_proj_f32(int L, const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1,
                                 float* ps, float* ps_halo, float* pr, hipStream_t st);
 hipError_t launch_node_proj(int L, const void* v16, int64_t n_local, const Lin& w1, float* proj, hipStream_t st);
+// The receiver halves of the owned rows only (bf16, latent 64 / 128), which is
+// all that the row-split forward reads.
+hipError_t launch_node_proj_r(int L, const void* v16, int64_t n_owned, const Lin& w1, float* proj, hipStream_t st);
 // bf16, l = 256: the edge forward and backward in row-split form with the
 // weights streamed through LDS (the forward, and a backward that recomputes
 // h_1, need the node projections of launch_node_proj for the block).

@@ -14,8 +14,9 @@
 //   input_grad         node gradients through that Linear's sender/receiver
 //                      blocks: ordered per-node sums of dz_0 (transposed CSR
 //                      for senders), then one node-level product
-//   dw / dw_reduce     weight gradients as split-K MFMA GEMMs, fixed order
-//   vec_reduce         bias and LayerNorm gradients, fixed order
+//   dw_stream          weight gradients of 128- and 256-wide layers over many
+//                      rows, fixed order (the others, the biases' and
+//                      LayerNorm's: dw.hip)
 //   mse                masked mean-squared-error loss and its gradient
 // No float atomics anywhere: every sum has a fixed order, so results are
 // bitwise reproducible run to run.
@@ -1654,6 +1655,42 @@ __device__ __forceinline__ void rt_first_layer(const uint4 (&ef)[L / 32], const 
   }
 }
 
+// The same with P_s[s] formed here from the sender's bf16 row (the product
+// node_proj_kernel takes of it, so the same bits).  The forward is bound by its
+// traffic, of which the gathered fp32 P_s rows, 512 bytes an edge at l = 128
+// and mostly L2 misses, were a third, while the matrix pipe was busy 12 %: half
+// the bytes for half again the products.  13.7M edges 2.62 -> 2.40 ms; 10.5M
+// edges with the h_1 stash 2.04 -> 1.79; and the projections need the receiver
+// half only (1M nodes 302 -> 199 us).
+template <int L>
+__device__ __forceinline__ void rt_first_layer_sg(const uint4 (&ef)[L / 32], const uint4* W1e, const uint4* W1s,
+                                                  const RsMeta& mt, bool ok, const uint16_t* __restrict__ V16,
+                                                  const float* __restrict__ proj, floatx4 (&z)[L / 16], int lane) {
+  constexpr int NB = L / 16, NKH = L / 32;
+  const int q = lane >> 4;
+  // rows past the tile's end gather node 0 (their results are never used)
+  const uint16_t* sp = V16 + (int64_t)(ok ? mt.s : 0) * L + q * 8;
+  const float* rp = proj + (int64_t)(ok ? mt.r : 0) * (2 * L) + L;
+  uint4 vs[NKH];
+  float4 pr[NB];
+#pragma unroll
+  for (int kg = 0; kg < NKH; ++kg) vs[kg] = *reinterpret_cast<const uint4*>(sp + kg * 32);
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) pr[cb] = rt_ld4(rp, cb, q);
+  // the gathers issue before the products, which then hide their latency
+  __builtin_amdgcn_sched_barrier(0);
+  rt_gemm<NB, NKH>(W1e, ef, z, lane);
+  floatx4 ps[NB];
+  rt_gemm<NB, NKH>(W1s, vs, ps, lane);
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) {
+    z[cb][0] = (z[cb][0] + ps[cb][0]) + pr[cb].x;
+    z[cb][1] = (z[cb][1] + ps[cb][1]) + pr[cb].y;
+    z[cb][2] = (z[cb][2] + ps[cb][2]) + pr[cb].z;
+    z[cb][3] = (z[cb][3] + ps[cb][3]) + pr[cb].w;
+  }
+}
+
 // Accumulator tile -> bf16 scratch (row order, swizzled) -> A fragments.
 template <int L>
 __device__ __forceinline__ void rs_to_frags(const float (&v)[L / 16][4], uint16_t* scr, uint4 (&f)[L / 32], int lane) {
@@ -1710,7 +1747,7 @@ struct RsFwdLay {
   static constexpr int W = NB * NKH * 64 * 16;         // bytes of one L x L packed layer
   static constexpr int SCR = 16 * 64 * 4;              // per-wave scratch: 16 rows x 64 fp32 columns
   // vectors: last bias, gamma, beta[, hidden bias]
-  static constexpr int OFF_W1 = 0, OFF_WH = W, OFF_WL = (D - 1) * W, OFF_VEC = D * W;
+  static constexpr int OFF_W1 = 0, OFF_WH = W, OFF_WL = (D - 1) * W, OFF_WS = D * W, OFF_VEC = (D + 1) * W;
   static constexpr int NVEC = (D == 3 ? 4 : 3) * L;
   static constexpr int OFF_SCR = OFF_VEC + NVEC * 4;
   // 12 waves per workgroup (at most 168 registers each: a tile's gathers are
@@ -1731,13 +1768,15 @@ __global__ __launch_bounds__((RsFwdLay<L, D>::NTH)) void edge_fwd_rs_kernel(Edge
   uint4* W1 = reinterpret_cast<uint4*>(lds + Lay::OFF_W1);
   uint4* WH = reinterpret_cast<uint4*>(lds + Lay::OFF_WH);
   uint4* WL = reinterpret_cast<uint4*>(lds + Lay::OFF_WL);
+  uint4* WS = reinterpret_cast<uint4*>(lds + Lay::OFF_WS);
   float* vbl = reinterpret_cast<float*>(lds + Lay::OFF_VEC);  // last bias
   float* vg = vbl + L;                                          // gamma
   float* vbt = vbl + 2 * L;                                     // beta
   float* vbh = vbl + 3 * L;                                     // hidden bias (D = 3)
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr32 = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
-  rs_copy_frags(W1, a.mlp.lin[0].wf, NB, NKH, 3 * NKH, 0);  // B operand read from memory rows
+  rs_copy_frags(W1, a.mlp.lin[0].wf, NB, NKH, 3 * NKH, 0);  // B operands read from memory rows
+  rs_copy_frags(WS, a.mlp.lin[0].wf, NB, NKH, 3 * NKH, NKH);
   if constexpr (D == 3) rt_copy_frags(WH, a.mlp.lin[1].wf, NB, NKH, NKH, 0);
   rt_copy_frags(WL, a.mlp.lin[D - 1].wf, NB, NKH, NKH, 0);
   rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
@@ -1773,7 +1812,7 @@ __global__ __launch_bounds__((RsFwdLay<L, D>::NTH)) void edge_fwd_rs_kernel(Edge
 #pragma unroll
     for (int kg = 0; kg < NKH; ++kg) ef[kg] = *reinterpret_cast<const uint4*>(erow + kg * 32 + q * 8);
     floatx4 z[NB];
-    rt_first_layer<L>(ef, W1, mt, ok, a.proj, z, ln);
+    rt_first_layer_sg<L>(ef, W1, WS, mt, ok, reinterpret_cast<const uint16_t*>(a.V16), a.proj, z, ln);
     float h[NB][4];
 #pragma unroll
     for (int cb = 0; cb < NB; ++cb)
@@ -2218,7 +2257,8 @@ __global__ __launch_bounds__(RS_NTH) void edge_bwd_rs_kernel(EdgeBwdArgs a) {
 // P[n] = [W_s v_n | W_r v_n + b_1] for the local nodes (T form, plain
 // column order): the sender and receiver blocks of the edge MLP's first
 // Linear on the bf16 block input, fp32 sums.
-template <int L>
+// SIDE0 = 1: the receiver half only.
+template <int L, int SIDE0>
 __global__ __launch_bounds__(RS_NTH) void node_proj_kernel(const uint16_t* __restrict__ V16, int64_t n_local, Lin w1,
                                                            float* __restrict__ proj) {
   constexpr int NKH = L / 32, NB = L / 16;
@@ -2226,7 +2266,7 @@ __global__ __launch_bounds__(RS_NTH) void node_proj_kernel(const uint16_t* __res
   extern __shared__ __align__(16) unsigned char lds[];
   uint4* WS = reinterpret_cast<uint4*>(lds);
   uint4* WR = reinterpret_cast<uint4*>(lds + W);
-  rs_copy_frags(WS, w1.wf, NB, NKH, 3 * NKH, NKH);
+  if constexpr (SIDE0 == 0) rs_copy_frags(WS, w1.wf, NB, NKH, 3 * NKH, NKH);
   rs_copy_frags(WR, w1.wf, NB, NKH, 3 * NKH, 2 * NKH);
   __syncthreads();
   const int wave = wave_id(), lane = threadIdx.x & 63;
@@ -2242,7 +2282,7 @@ __global__ __launch_bounds__(RS_NTH) void node_proj_kernel(const uint16_t* __res
 #pragma unroll
     for (int kg = 0; kg < NKH; ++kg) vf[kg] = *reinterpret_cast<const uint4*>(V16 + src * L + kg * 32 + q * 8);
 #pragma unroll
-    for (int side = 0; side < 2; ++side) {
+    for (int side = SIDE0; side < 2; ++side) {
       floatx4 acc[NB];
       rt_gemm<NB, NKH>(side == 0 ? WS : WR, vf, acc, ln);
       if (side == 1) {  // the first Linear's bias rides with the receiver half
@@ -5914,19 +5954,26 @@ static hipError_t edge_bwd_rs_t(const EdgeBwdArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int L>
+template <int L, int SIDE0>
 static hipError_t node_proj_t(const void* v16, int64_t n_local, const Lin& w1, float* proj, hipStream_t st) {
   constexpr int W = (L / 16) * (L / 32) * 64 * 16;
-  allow_lds(node_proj_kernel<L>, 2 * W);
-  hipLaunchKernelGGL((node_proj_kernel<L>), dim3(RS_GRID), dim3(RS_NTH), 2 * W, st,
+  allow_lds(node_proj_kernel<L, SIDE0>, 2 * W);
+  hipLaunchKernelGGL((node_proj_kernel<L, SIDE0>), dim3(RS_GRID), dim3(RS_NTH), 2 * W, st,
                      reinterpret_cast<const uint16_t*>(v16), n_local, w1, proj);
   return hipGetLastError();
 }
 
+hipError_t launch_node_proj_r(int L, const void* v16, int64_t n_owned, const Lin& w1, float* proj, hipStream_t st) {
+  if (n_owned == 0) return hipSuccess;
+  if (L == 64) return node_proj_t<64, 1>(v16, n_owned, w1, proj, st);
+  if (L == 128) return node_proj_t<128, 1>(v16, n_owned, w1, proj, st);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_node_proj(int L, const void* v16, int64_t n_local, const Lin& w1, float* proj, hipStream_t st) {
   if (n_local == 0) return hipSuccess;
-  if (L == 64) return node_proj_t<64>(v16, n_local, w1, proj, st);
-  if (L == 128) return node_proj_t<128>(v16, n_local, w1, proj, st);
+  if (L == 64) return node_proj_t<64, 0>(v16, n_local, w1, proj, st);
+  if (L == 128) return node_proj_t<128, 0>(v16, n_local, w1, proj, st);
   if (L == 256) {
     allow_lds(node_proj_rw_kernel, RwProjLay::END);
     hipLaunchKernelGGL(node_proj_rw_kernel, dim3(RS_GRID), dim3(RwProjLay::NTH), RwProjLay::END, st,
