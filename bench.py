@@ -48,6 +48,11 @@ def algorithmic(timer: str, cfg, E: int, No: int, Nh: int, lean: bool = False, s
         # [e | v_s | v_r] times W_1 per edge; ts bytes per stored element,
         # node rows gathered from the fp32 latents or their bf16 copy
         ts = 2 if cfg.precision == "bf16" else 4
+        if timer == "edge_fwd" and cfg.precision == "fp32" and (l == 64 or (l == 128 and D == 2)):
+            # fp32 row-split kernels: node columns applied once per node;
+            # read e^k, ids, P_s, P_r; write e^{k+1}, h_1 (unless lean) and agg
+            by = E * ((2 if lean else 3) * ts * l + 8) + Nl * ts * l + No * ts * l * 2
+            return by, E * 2 * l * l * D
         if timer == "edge_fwd":
             # read e^k, ids, node rows; write e^{k+1}, h_1 (kept for the
             # backward unless lean) and agg
@@ -77,7 +82,9 @@ def algorithmic(timer: str, cfg, E: int, No: int, Nh: int, lean: bool = False, s
         by -= stash * (E * 2 * l + Nl * 2 * l * 4)
         return by, E * (4 - stash) * 2 * l * l
     if timer == "edge_fwd":
-        # read e^k, ids, projections; write e^{k+1} and agg (and h_1 with the stash)
+        # read e^k, ids, projections; write e^{k+1} and agg (and h_1 with the stash).
+        # (The kernel reads the senders' bf16 rows in place of their
+        # projections and takes W_s per edge; the compulsory work is this.)
         by = E * (2 * l + 8 + 2 * l) + Nl * 2 * l * 4 + No * l * 4 + stash * E * 2 * l
         return by, E * 2 * 2 * l * l
     if timer == "node_proj":
