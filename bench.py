@@ -88,7 +88,9 @@ def algorithmic(timer: str, cfg, E: int, No: int, Nh: int, lean: bool = False, s
         by = E * (2 * l + 8 + 2 * l) + Nl * 2 * l * 4 + No * l * 4 + stash * E * 2 * l
         return by, E * 2 * 2 * l * l
     if timer == "node_proj":
-        return Nl * (2 * l + 2 * l * 4), Nl * 2 * l * 2 * l
+        # both halves of every local row, or (stashed blocks) the owned rows' receiver half
+        part = (1 - stash) * Nl * 2 + stash * No
+        return ((1 - stash) * Nl + stash * No) * 2 * l + part * l * 4, part * 2 * l * l
     if timer == "input_grad":
         # dz_0 rows through the transposed CSR, receiver sums, dv (read and
         # write), halo gradients, sender sums out
