@@ -631,7 +631,7 @@ hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p,
   if (p.f32) {
     float* ps = p.infer ? (float*)(ws + p.V) + (size_t)((k + 1) & 1) * no * L : (float*)(ws + p.DZS);
     float* ps_halo = p.infer ? (float*)(ws + p.PSH) : ps + (size_t)no * L;
-    {
+    if (g.n_edges > 0) {
       Timed t_(m, MGN_T_NODE_PROJ, st);
       e = launch_node_proj_f32(L, v, ea.H, no, nh, ea.mlp.lin[0], ps, ps_halo, agg, st);
       if (e != hipSuccess) return e;

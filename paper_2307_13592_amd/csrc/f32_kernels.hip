@@ -233,9 +233,9 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
   float* vbh = vbl + 3 * L;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
-  int64_t r0 = 0, r1 = 0, E0 = 0, E1 = 0;
-  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, 0, a.n_owned, 0, n_edges, nact, r0, r1, E0, E1);
-  rs_zero_empty(a.row_ptr, r0, r1, a.agg, L);
+  int64_t E0 = 0, E1 = 0;
+  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, 0, n_edges, nact, E0, E1);
+  rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
   tf_copy_frags<NB, 3 * NB, TF_NTH>(W1, a.mlp.lin[0].wf, 0);
   if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
   tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
@@ -350,9 +350,9 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
   float* vbh = vbl + 2 * L;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
-  int64_t r0 = a.r_lo, r1 = a.r_lo, E0 = 0, E1 = 0;
-  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, a.r_lo, a.r_hi, a.e_base, n_edges, nact, r0, r1, E0, E1);
-  rs_zero_empty(a.row_ptr, r0, r1, a.dagg, L);
+  int64_t E0 = 0, E1 = 0;
+  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, a.e_base, n_edges, nact, E0, E1);
+  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
   tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
   if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
   tf_copy_frags<NB, NB, TF_NTH>(W1, a.mlp.lin[0].wb, 0);  // e block: the first NB column blocks

@@ -1786,7 +1786,7 @@ __global__ __launch_bounds__((RsFwdLay<L, D>::NTH)) void edge_fwd_rs_kernel(Edge
   __syncthreads();
   int64_t r0, r1;
   rs_range(a.row_ptr, 0, a.n_owned, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, r0, r1, a.agg, L);
+  rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
   uint16_t* Eout = reinterpret_cast<uint16_t*>(a.Eout);
@@ -1966,7 +1966,7 @@ __global__ __launch_bounds__(RS_NTH) void edge_bwd_rs_kernel(EdgeBwdArgs a) {
   __syncthreads();
   int64_t r0, r1;
   rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, r0, r1, a.dagg, L);
+  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
   // column totals of the bias / LayerNorm gradients (rt_col_totals' share of
@@ -2508,7 +2508,7 @@ void edge_fwd_rw_kernel(EdgeFwdArgs a) {
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   int64_t r0, r1;
   rs_range(a.row_ptr, 0, a.n_owned, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, r0, r1, a.agg, L);
+  rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
   // wave-uniform bounds, kept in scalar registers
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);
   const int ntile = rw_max_tiles((int)((E1 - E0 + TE - 1) / TE), reinterpret_cast<int*>(lds + Lay::OFF_SLOT));
@@ -2791,7 +2791,7 @@ void edge_bwd_rw_kernel(EdgeBwdArgs a) {
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   int64_t r0, r1;
   rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, r0, r1, a.dagg, L);
+  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const int ntile = rw_max_tiles((int)((E1 - E0 + 15) / 16), reinterpret_cast<int*>(lds + Lay::OFF_SLOT));
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
