@@ -75,6 +75,7 @@ struct mgn_model {
   bool graph_ok = false;
   mgn_graph vg{};
   std::vector<int32_t> rp_host;
+  int64_t max_degree = 0;  // its largest receiver, in edges
   int ckpt = 0;                 // edge-stream checkpoint interval (0: keep every block)
   int h1_stash = 0;             // row-split kernels: blocks whose first-Linear ReLU output the forward keeps
   bool infer = false;           // forward-only plan (mgn_set_inference)
@@ -494,6 +495,8 @@ mgn_status mgn_graph_validate(mgn_model* m, const mgn_graph* g, mgn_stream strea
   m->vg = *g;
   m->graph_ok = true;
   m->rp_host = std::move(rp);
+  m->max_degree = 0;
+  for (int64_t r = 0; r < no; ++r) m->max_degree = std::max<int64_t>(m->max_degree, m->rp_host[r + 1] - m->rp_host[r]);
   return MGN_OK;
 }
 
@@ -640,7 +643,7 @@ hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p,
     ea.ps_halo = ps_halo;
     ea.pr = agg;
     Timed t_(m, MGN_T_EDGE_FWD, st);
-    return launch_edge_fwd_f32(L, D, ea, g.n_edges, st);
+    return launch_edge_fwd_f32(L, D, ea, g.n_edges, m->max_degree, st);
   }
   Timed t_(m, MGN_T_EDGE_FWD, st);
   return launch_edge_fwd(m->prec, L, D, ea, FWD_EDGE_GRID, st);
@@ -1141,7 +1144,7 @@ struct Bwd {
         a.e_base = e0;
         {
           Timed t_(m, MGN_T_EDGE_BWD, st);
-          e = p.f32 ? launch_edge_bwd_f32(L, D, a, rows, st)
+          e = p.f32 ? launch_edge_bwd_f32(L, D, a, rows, m->max_degree, st)
               : edge_wide(m->prec, L, D, rows) ? launch_edge_bwd_wide(D, a, rows, st)
                                                : launch_edge_bwd(m->prec, L, D, a, BWD_GRID, st);
         }

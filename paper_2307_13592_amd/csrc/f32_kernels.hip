@@ -108,15 +108,16 @@ __device__ __forceinline__ void tf_gemm_t(const float* Wl, const float4 (&X)[NB]
 }
 
 // A tile's metadata as rt_meta_load, rows past the range end repeating the
-// range's last edge (their results are never used).
+// range's last edge (their results are never used).  past: what follows the
+// range's last edge.
 __device__ __forceinline__ RsMetaRaw tf_meta_load(const int32_t* __restrict__ erecv, const int32_t* __restrict__ send,
-                                                  int64_t sb, int64_t e1) {
+                                                  int64_t sb, int64_t e1, int32_t past) {
   const int64_t e = sb + (threadIdx.x & 15);
   const int64_t i = e < e1 ? e : e1 - 1;
   RsMetaRaw w;
   w.r = erecv[i];
   w.s = send[i];
-  w.rn = e + 1 < e1 ? erecv[e + 1] : -1;
+  w.rn = e + 1 < e1 ? erecv[e + 1] : past;
   return w;
 }
 __device__ __forceinline__ RsMeta tf_meta_make(const RsMetaRaw& w, int n) {
@@ -125,15 +126,50 @@ __device__ __forceinline__ RsMeta tf_meta_make(const RsMetaRaw& w, int n) {
   return mt;
 }
 
+// A wave's edges [E0, E1).  SPLIT, for graphs with very large receivers: the
+// workgroup takes whole receivers, its waves an even share of the 16-edge
+// tiles each, so a receiver's edges may go on from one wave to the next.
+// Otherwise each of the nact working waves takes whole receivers.
+struct TfRange {
+  int64_t E0, E1;
+  int32_t past;     // receiver id after the last edge that does not end a sum: the last edge's own, if it goes on; else -1
+  bool open;        // the first receiver's edges began in an earlier wave, and their end has not been reached
+};
+template <bool SPLIT>
+__device__ __forceinline__ TfRange tf_range(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ erecv,
+                                            int64_t e_lo, int64_t E, int nact) {
+  const int wave = wave_id();
+  TfRange r{0, 0, -1, false};
+  if constexpr (SPLIT) {
+    int64_t B0, B1;
+    rs_range_e(row_ptr, erecv, e_lo, E, 1, 0, B0, B1);
+    const int64_t T = (B1 - B0 + 15) / 16;
+    r.E0 = B0 + 16 * (T * wave / TF_NWV);
+    r.E1 = wave + 1 == TF_NWV ? B1 : B0 + 16 * (T * (wave + 1) / TF_NWV);
+    if (r.E0 < r.E1) {
+      const int32_t last = erecv[r.E1 - 1];
+      if (r.E1 < B1 && erecv[r.E1] == last) r.past = last;
+      r.open = r.E0 > B0 && erecv[r.E0 - 1] == erecv[r.E0];
+    }
+    r.past = __builtin_amdgcn_readfirstlane(r.past);
+    r.open = __builtin_amdgcn_readfirstlane(r.open) != 0;
+  } else if (wave < nact) {
+    rs_range_e(row_ptr, erecv, e_lo, E, nact, wave, r.E0, r.E1);
+  }
+  return r;
+}
+
 // Ordered receiver sums of a tile's values v (columns 16 cb + 4 q + r of row
 // e): 64 columns at a time through the wave's 2 KiB scratch, 32 of them per
 // half (lanes 0..31, then 32..63), so that two L x L weight matrices leave
 // room for eight waves' scratch at L = 128.  Each lane carries the running sum
-// of column ln + 64 j; a segment's total is stored at its last row.
-template <int L>
+// of column ln + 64 j; a segment's total is stored at its last row.  SPLIT: the
+// end of a segment that an earlier wave began (open) goes to head instead.
+template <int L, bool SPLIT>
 __device__ __forceinline__ void tf_segment_sums(const float4 (&v)[L / 16], float* scr, const RsMeta& mt, int n, int ln,
-                                                float (&run)[L / 64], float* dst) {
+                                                float (&run)[L / 64], float* dst, float (&head)[L / 64], bool& open) {
   const int e = ln & 15, q = ln >> 4;
+  const int first = SPLIT && open && mt.last ? __builtin_ctzll(mt.last) : -1;
 #pragma unroll
   for (int j = 0; j < L / 64; ++j) {
     float x[16];
@@ -152,11 +188,47 @@ __device__ __forceinline__ void tf_segment_sums(const float4 (&v)[L / 16], float
       if (row < n) {
         run[j] += x[row];
         if ((mt.last >> row) & 1ull) {
-          dst[(int64_t)__builtin_amdgcn_readlane(mt.r, row) * L + ln + 64 * j] = run[j];
+          if (SPLIT && row == first) head[j] = run[j];
+          else dst[(int64_t)__builtin_amdgcn_readlane(mt.r, row) * L + ln + 64 * j] = run[j];
           run[j] = 0.f;
         }
       }
     }
+  }
+  if (SPLIT && first >= 0) open = false;
+}
+
+// SPLIT, after a workgroup's last tile: the sums of the receivers whose edges
+// went on from one wave to the next, in wave order, by the wave in which they
+// began.  run: what the wave's last, unended segment came to.  lds:
+// 2 * TF_NWV * L floats and TF_NWV words, free to overwrite.
+template <int L>
+__device__ __forceinline__ void tf_join(const TfRange& r, bool open, const float (&head)[L / 64],
+                                        const float (&run)[L / 64], unsigned char* lds, float* dst) {
+  const int wave = wave_id(), lane = threadIdx.x & 63;
+  float* H = reinterpret_cast<float*>(lds);
+  float* T = H + TF_NWV * L;
+  int* on = reinterpret_cast<int*>(T + TF_NWV * L);
+  // no segment ended in the wave (or it had no edges): its run is the middle of a sum
+  const bool through = open || r.E0 >= r.E1;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < L / 64; ++j) {
+    H[wave * L + lane + 64 * j] = head[j];
+    T[wave * L + lane + 64 * j] = run[j];
+  }
+  if (lane == 0) on[wave] = through;
+  __syncthreads();
+  if (through || r.past < 0) return;
+  // the receiver ends in a later wave of the workgroup, so the loop meets its head
+#pragma unroll
+  for (int j = 0; j < L / 64; ++j) {
+    float s = run[j];
+    for (int u = wave + 1; u < TF_NWV; ++u) {
+      s += (on[u] ? T : H)[u * L + lane + 64 * j];
+      if (!on[u]) break;
+    }
+    dst[(int64_t)r.past * L + lane + 64 * j] = s;
   }
 }
 
@@ -219,7 +291,7 @@ struct TfFwdLay {
 // kernel, which applies the whole 3L x L first Linear per edge).  P_r may share its rows with a.agg: a
 // receiver's row is read with its edges' tiles and its sum stored after them,
 // by the same wave.
-template <int L, int D>
+template <int L, int D, bool SPLIT>
 __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int64_t n_edges, int nact) {
   using Lay = TfFwdLay<L, D>;
   constexpr int NB = Lay::NB;
@@ -233,8 +305,9 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
   float* vbh = vbl + 3 * L;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
-  int64_t E0 = 0, E1 = 0;
-  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, 0, n_edges, nact, E0, E1);
+  const TfRange rg = tf_range<SPLIT>(a.row_ptr, a.erecv, 0, n_edges, nact);
+  const int64_t E0 = rg.E0, E1 = rg.E1;
+  bool open = rg.open;
   rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
   tf_copy_frags<NB, 3 * NB, TF_NTH>(W1, a.mlp.lin[0].wf, 0);
   if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
@@ -244,11 +317,11 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
   rt_copy_vec(vbt, a.mlp.beta, L);
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   __syncthreads();
-  if (E0 >= E1) return;
+  if (!SPLIT && E0 >= E1) return;
   const float* Ein = reinterpret_cast<const float*>(a.Ein);
   float* Eout = reinterpret_cast<float*>(a.Eout);
   float* hid = reinterpret_cast<float*>(a.hid_out);
-  float run[L / 64] = {};
+  float run[L / 64] = {}, head[L / 64] = {};
   // e^k rows of a tile are loaded while the tile before runs its last
   // product, the P rows at the tile's start: they are added after its first
   // product, which hides them.  So no product waits for a load, nor, through
@@ -258,8 +331,11 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
   auto load_e = [&](int64_t sb, int ln) {
     tf_load<NB>(Ein + (sb + (ln & 15) < E1 ? sb + (ln & 15) : E1 - 1) * L, ln >> 4, ef);
   };
-  RsMetaRaw cur = tf_meta_load(a.erecv, a.send, E0, E1);
-  load_e(E0, lane);
+  RsMetaRaw cur{};
+  if (!SPLIT || E0 < E1) {
+    cur = tf_meta_load(a.erecv, a.send, E0, E1, rg.past);
+    load_e(E0, lane);
+  }
   for (int64_t sb = E0; sb < E1; sb += 16) {
     int ln = lane;  // an opaque copy: lane-dependent addresses are formed per tile, not kept in registers
     asm volatile("" : "+v"(ln));
@@ -270,7 +346,7 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
     float4 ps[NB], pr[NB];
     tf_load<NB>(mt.s < a.n_owned ? a.ps + (int64_t)mt.s * L : a.ps_halo + ((int64_t)mt.s - a.n_owned) * L, q, ps);
     tf_load<NB>(a.pr + (int64_t)mt.r * L, q, pr);
-    cur = tf_meta_load(a.erecv, a.send, sb + 16, E1);
+    cur = tf_meta_load(a.erecv, a.send, sb + 16, E1, rg.past);
     __builtin_amdgcn_sched_barrier(0);
     floatx4 acc[NB];
     tf_gemm<NB>(W1, ef, acc, slot);
@@ -311,8 +387,9 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
         ek[cb] = make_float4(ek[cb].x + y[cb].x, ek[cb].y + y[cb].y, ek[cb].z + y[cb].z, ek[cb].w + y[cb].w);
       tf_store<NB>(Eout + (sb + e) * L, q, ek);
     }
-    tf_segment_sums<L>(y, scr, mt, n, ln, run, a.agg);
+    tf_segment_sums<L, SPLIT>(y, scr, mt, n, ln, run, a.agg, head, open);
   }
+  if constexpr (SPLIT) tf_join<L>(rg, open, head, run, lds, a.agg);
 }
 
 // ----------------------------------------------------------- edge backward ---
@@ -337,7 +414,7 @@ struct TfBwdLay {
 // layers after the first recomputed, LayerNorm backward, the data gradients
 // down to dz_0, de^k = de^{k+1} + dz_0 W_e, receiver sums of dz_0 over the
 // consumed dagg rows, per-workgroup bias / LayerNorm partials.
-template <int L, int D>
+template <int L, int D, bool SPLIT>
 __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int64_t n_edges, int nact) {
   using Lay = TfBwdLay<L, D>;
   constexpr int NB = Lay::NB, NV = 4 * NB, NR = NV / 16;
@@ -350,8 +427,9 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
   float* vbh = vbl + 2 * L;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
-  int64_t E0 = 0, E1 = 0;
-  if (wave < nact) rs_range_e(a.row_ptr, a.erecv, a.e_base, n_edges, nact, E0, E1);
+  const TfRange rg = tf_range<SPLIT>(a.row_ptr, a.erecv, a.e_base, n_edges, nact);
+  const int64_t E0 = rg.E0, E1 = rg.E1;
+  bool open = rg.open;
   rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
   tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
   if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
@@ -384,7 +462,7 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
   const float* hin = reinterpret_cast<const float*>(a.hid_in);
   const float* dnx = reinterpret_cast<const float*>(a.de_next);
   float* deo = reinterpret_cast<float*>(a.de_out);
-  float run[L / 64] = {};
+  float run[L / 64] = {}, head[L / 64] = {};
   // h_1 rows of a tile are loaded while the tile before runs its last
   // product, de^{k+1} (the last block has none: its loads re-read the h_1 rows
   // and are replaced by zeros) and dagg at the tile's start, used after its
@@ -395,7 +473,7 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
   };
   RsMetaRaw cur{};
   if (E0 < E1) {
-    cur = tf_meta_load(a.erecv, a.send, E0, E1);
+    cur = tf_meta_load(a.erecv, a.send, E0, E1, rg.past);
     load_h1(E0, lane);
   }
   for (int64_t sb = E0; sb < E1; sb += 16) {
@@ -409,7 +487,7 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
     float4 de[NB], dm[NB];
     tf_load<NB>((dnx ? dnx : hin) + (sb + (ok ? e : n - 1)) * L, q, de);
     tf_load<NB>(a.dagg + (int64_t)mt.r * L, q, dm);
-    cur = tf_meta_load(a.erecv, a.send, sb + 16, E1);
+    cur = tf_meta_load(a.erecv, a.send, sb + 16, E1, rg.past);
     __builtin_amdgcn_sched_barrier(0);
     uint32_t mask[2] = {0u, 0u};  // ReLU derivative of the hidden layers, bit cb * 4 + r
 #pragma unroll
@@ -500,8 +578,9 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
       for (int cb = 0; cb < NB; ++cb) de[cb] = tf_add(acc[cb], de[cb]);
       tf_store<NB>(deo + (sb + e) * L, q, de);
     }
-    tf_segment_sums<L>(v, scr, mt, n, ln, run, a.dagg);
+    tf_segment_sums<L, SPLIT>(v, scr, mt, n, ln, run, a.dagg, head, open);
   }
+  if constexpr (SPLIT) tf_join<L>(rg, open, head, run, lds, a.dagg);
   // column partials: lane (e, q)'s totals are columns 16 cb + 4 q + r for
   // index e * NR + t = 4 cb + r; then the waves in order through LDS (the
   // weight area is free now)
@@ -1189,22 +1268,34 @@ void allow_lds(F* fn, int bytes) {
 // workgroup) left some waves two tiles: forward 27.8 us.
 int tf_waves(int64_t edges) { return edges <= (int64_t)4 * RS_GRID * 11 ? 4 : TF_NWV; }
 
-template <int L, int D>
+template <int L, int D, bool SPLIT>
 hipError_t edge_fwd_f32_t(const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st) {
   using Lay = TfFwdLay<L, D>;
-  allow_lds(edge_fwd_f32_kernel<L, D>, Lay::END);
-  hipLaunchKernelGGL((edge_fwd_f32_kernel<L, D>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
+  allow_lds(edge_fwd_f32_kernel<L, D, SPLIT>, Lay::END);
+  hipLaunchKernelGGL((edge_fwd_f32_kernel<L, D, SPLIT>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
                      n_edges, tf_waves(n_edges));
   return hipGetLastError();
 }
-template <int L, int D>
+template <int L, int D, bool SPLIT>
 hipError_t edge_bwd_f32_t(const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st) {
   using Lay = TfBwdLay<L, D>;
-  allow_lds(edge_bwd_f32_kernel<L, D>, Lay::END);
-  hipLaunchKernelGGL((edge_bwd_f32_kernel<L, D>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
+  allow_lds(edge_bwd_f32_kernel<L, D, SPLIT>, Lay::END);
+  hipLaunchKernelGGL((edge_bwd_f32_kernel<L, D, SPLIT>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
                      n_edges, tf_waves(n_edges));
   return hipGetLastError();
 }
+
+// Whether one receiver's edges are more than a wave should take alone: over
+// twice the share of each, and four tiles.  At l = 128, two blocks forward and
+// backward on 259,000 edges (share 126): largest receiver 300 edges 3.00 ms
+// with a wave alone on it, 2.34 split; 10,000 edges 34.3 and 9.1.  On 2.7M
+// edges (share 1,340): 1,000 edges 20.0 ms alone, 18.4 without that receiver;
+// 3,000 edges 29.9 and 19.6.
+bool tf_split(int64_t edges, int64_t max_degree) {
+  const int64_t share = edges / (RS_GRID * TF_NWV);
+  return max_degree > (share > 32 ? 2 * share : 64);
+}
+
 template <int L>
 hipError_t node_proj_f32_t(const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1, float* ps,
                            float* ps_halo, float* pr, hipStream_t st) {
@@ -1316,15 +1407,25 @@ hipError_t launch_rows_bwd_f32(int L, int D, int kind, const RowsBwdArgs& a, hip
 
 bool edge_f32(int prec, int L, int D) { return prec == F32 && (L == 64 || (L == 128 && D == 2)); }
 
-hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st) {
-  if (L == 64) return D == 2 ? edge_fwd_f32_t<64, 2>(a, n_edges, st) : edge_fwd_f32_t<64, 3>(a, n_edges, st);
-  if (L == 128 && D == 2) return edge_fwd_f32_t<128, 2>(a, n_edges, st);
+hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, int64_t max_degree,
+                               hipStream_t st) {
+  const bool split = tf_split(n_edges, max_degree);
+#define EF(LL, DD) \
+  if (L == LL && D == DD) \
+    return split ? edge_fwd_f32_t<LL, DD, true>(a, n_edges, st) : edge_fwd_f32_t<LL, DD, false>(a, n_edges, st);
+  EF(64, 2) EF(64, 3) EF(128, 2)
+#undef EF
   return hipErrorInvalidValue;
 }
-hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st) {
+hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, int64_t max_degree,
+                               hipStream_t st) {
   if (!a.hid_in) return hipErrorInvalidValue;
-  if (L == 64) return D == 2 ? edge_bwd_f32_t<64, 2>(a, n_edges, st) : edge_bwd_f32_t<64, 3>(a, n_edges, st);
-  if (L == 128 && D == 2) return edge_bwd_f32_t<128, 2>(a, n_edges, st);
+  const bool split = tf_split(n_edges, max_degree);
+#define EB(LL, DD) \
+  if (L == LL && D == DD) \
+    return split ? edge_bwd_f32_t<LL, DD, true>(a, n_edges, st) : edge_bwd_f32_t<LL, DD, false>(a, n_edges, st);
+  EB(64, 2) EB(64, 3) EB(128, 2)
+#undef EB
   return hipErrorInvalidValue;
 }
 hipError_t launch_node_proj_f32(int L, const float* V, const float* H, int64_t n_owned, int64_t n_halo, const Lin& w1,

@@ -230,9 +230,12 @@ bool edge_rs(int prec, int L, int D);
 // fp32 row-split edge kernels and their node projections (f32_kernels.hip):
 // latent 64, or 128 at MLP depth 2.  The forward takes EdgeFwdArgs::ps .. pr;
 // the backward starts from the forward's first-Linear ReLU output (hid_in).
+// max_degree: the graph's largest receiver, in edges.
 bool edge_f32(int prec, int L, int D);
-hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st);
-hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, hipStream_t st);
+hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, int64_t max_degree,
+                               hipStream_t st);
+hipError_t launch_edge_bwd_f32(int L, int D, const EdgeBwdArgs& a, int64_t n_edges, int64_t max_degree,
+                               hipStream_t st);
 // fp32 row kernels in T form: encoders of at most 16 features and the node
 // half, latent 64 or 128 (forward: not 128 at depth 3).  The edge encoder's backward forms the
 // first Linear's weight gradient itself for at most 4 features (w1_part, that

@@ -56,14 +56,15 @@ __device__ __forceinline__ void rs_range(const int32_t* __restrict__ row_ptr, in
   r1 = q + 1 == W ? hi_r : find(e0 + E * (q + 1) / W);
 }
 
-// The edges [E0, E1) of this wave's receivers, of the edges [e_lo, e_lo + E)
-// (whole receivers), with the boundaries looked up through the per-edge
-// receiver ids: two dependent loads where the search above takes two per
-// halving of the receiver count (on a graph of 11,000 edges, half of an edge
-// kernel's time).  A boundary inside a receiver's edges moves past them.
+// The edges [E0, E1) of this wave's receivers (wave `wave` of nwv per
+// workgroup), of the edges [e_lo, e_lo + E) (whole receivers), with the
+// boundaries looked up through the per-edge receiver ids: two dependent loads
+// where the search above takes two per halving of the receiver count (on a
+// graph of 11,000 edges, half of an edge kernel's time).  A boundary inside a
+// receiver's edges moves past them.
 __device__ __forceinline__ void rs_range_e(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ erecv,
-                                           int64_t e_lo, int64_t E, int nwv, int64_t& E0, int64_t& E1) {
-  const int G = gridDim.x, b = blockIdx.x, wave = wave_id();
+                                           int64_t e_lo, int64_t E, int nwv, int wave, int64_t& E0, int64_t& E1) {
+  const int G = gridDim.x, b = blockIdx.x;
   const int64_t W = (int64_t)G * nwv;
   const int64_t q = ((int64_t)(b & 7) * (G >> 3) + (b >> 3)) * nwv + wave;
   const int64_t t0 = E * q / W, t1 = E * (q + 1) / W;

@@ -312,7 +312,7 @@ __global__ __launch_bounds__(W_NTH) __attribute__((amdgpu_waves_per_eu(2, 2))) v
   const int wave = wave_id(), lane = threadIdx.x & 63;
   uint16_t* scr = reinterpret_cast<uint16_t*>(lds + W_OFF_SCR + wave * 2048);
   int64_t E0, E1;
-  rs_range_e(a.row_ptr, a.recv, a.e_lo, a.rows, W_NWV, E0, E1);
+  rs_range_e(a.row_ptr, a.recv, a.e_lo, a.rows, W_NWV, wave, E0, E1);
   rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.sum, WL);
   wide_copy<true>(W, a.w, a.src_nkg);
   __syncthreads();
