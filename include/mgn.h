@@ -219,7 +219,10 @@ mgn_status mgn_norm_apply(const float* x, int64_t rows, int32_t cols, const doub
                           mgn_stream stream);
 
 /* Device workspace mgn_forward/mgn_backward need for graph g (bytes) under
- * the model's checkpointing setting. */
+ * the model's checkpointing setting.  For a forward-only fp32 plan with a halo
+ * this includes 4 * latent bytes per halo node that mgn_forward can do without
+ * (a smaller workspace is accepted by as much: slower, the same outputs),
+ * unless that would take it past MGN_NOALLOC_WS_MAX. */
 mgn_status mgn_workspace_size(const mgn_model* m, const mgn_graph* g, size_t* bytes);
 
 /* Forward pass of one partition: Algorithm 1's forward (EncNode, EncEdge,

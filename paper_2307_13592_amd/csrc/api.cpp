@@ -38,7 +38,10 @@ struct MlpL {
 
 struct WsPlan {
   size_t erecv, chunk, unit_r, nunits, V, V16, PROJ, AGG, ES, DV[2], DAGG, DZS, DE, DEL_E[3], HID_E[2], DEL_N[3], HID_N[2],
-      HID_NK, HID_E1, PART, VPART, SRANGE, PSH, vstride, total;
+      HID_NK, HID_E1, PART, VPART, SRANGE, vstride, total;
+  // forward-only, fp32 row-split kernels: room after `total` for the halo rows
+  // of the projections, used when the workspace has it
+  size_t halo_rows = 0;
   int64_t max_units;
   // edge-stream checkpointing: interval s (0: every block kept), checkpoints
   bool lean = false;
@@ -294,15 +297,12 @@ WsPlan make_plan(const mgn_model* m, const mgn_graph* g) {
   // fp32 row-split edge kernels: the projections take rows that are free while
   // the edge half of a block runs (P_r: the block's aggregates, stored after
   // they are read; P_s: the backward's per-sender sums, or, forward-only, the
-  // next node latents and rows of their own for the halo)
+  // next node latents and, where the workspace has room, rows of their own for
+  // the halo)
   p.f32 = edge_f32(m->prec, m->L, m->D);
   if (p.infer) {
-    const size_t psh = p.f32 ? al(4 * (size_t)g->n_halo * L) : 0;
-    // a graph that fits the static workspace of mgn_forward_noalloc without
-    // those halo rows only keeps the streaming kernel, so that it still runs
-    if (psh > 0 && o <= MGN_NOALLOC_WS_MAX && o + psh > MGN_NOALLOC_WS_MAX) p.f32 = false;
-    else p.PSH = take(psh);
     p.total = o;
+    p.halo_rows = p.f32 ? al(4 * (size_t)g->n_halo * L) : 0;
     return p;
   }
   p.DV[0] = take(4 * (size_t)no * L);
@@ -574,7 +574,9 @@ mgn_status mgn_workspace_size(const mgn_model* cm, const mgn_graph* g, size_t* b
   if (!bytes) return fail(m, MGN_E_ARG, "mgn_workspace_size: bytes is NULL");
   mgn_status s = check_graph_args(m, g);
   if (s) return s;
-  *bytes = make_plan(m, g).total;
+  const WsPlan p = make_plan(m, g);
+  // the optional halo rows do not push a graph past what mgn_forward_noalloc has
+  *bytes = p.total <= MGN_NOALLOC_WS_MAX && p.total + p.halo_rows > MGN_NOALLOC_WS_MAX ? p.total : p.total + p.halo_rows;
   return MGN_OK;
 }
 
@@ -633,10 +635,10 @@ hipError_t edge_forward_block(mgn_model* m, const mgn_graph& g, const WsPlan& p,
   }
   if (p.f32) {
     float* ps = p.infer ? (float*)(ws + p.V) + (size_t)((k + 1) & 1) * no * L : (float*)(ws + p.DZS);
-    float* ps_halo = p.infer ? (float*)(ws + p.PSH) : ps + (size_t)no * L;
+    float* ps_halo = !p.infer ? ps + (size_t)no * L : p.halo_rows ? (float*)(ws + p.total) : nullptr;
     if (g.n_edges > 0) {
       Timed t_(m, MGN_T_NODE_PROJ, st);
-      e = launch_node_proj_f32(L, v, ea.H, no, nh, ea.mlp.lin[0], ps, ps_halo, agg, st);
+      e = launch_node_proj_f32(L, v, ea.H, no, ps_halo ? nh : 0, ea.mlp.lin[0], ps, ps_halo, agg, st);
       if (e != hipSuccess) return e;
     }
     ea.ps = ps;
@@ -697,9 +699,10 @@ mgn_status fwd_begin(mgn_model* m, const mgn_graph* g, const float* nf, const fl
     return fail(m, MGN_E_ARG, f + ": misaligned pointer (features 4 bytes, halo 16 bytes)");
   if (!workspace || !aligned(workspace, 256))
     return fail(m, MGN_E_ARG, f + ": workspace NULL or not 256-byte aligned");
-  const WsPlan p = make_plan(m, g);
+  WsPlan p = make_plan(m, g);
   if (ws_bytes < p.total)
     return fail(m, MGN_E_NOMEM, f + ": workspace too small (need " + std::to_string(p.total) + " bytes)");
+  if (ws_bytes < p.total + p.halo_rows) p.halo_rows = 0;
   // the step's buffers, kept for the later stages and the backward
   m->fwd_done = false;
   m->fwd_next = -1;

@@ -81,6 +81,30 @@ __device__ __forceinline__ void tf_gemm(const float4* Wl, const float4 (&X)[NK],
   }
 }
 
+// The same from the packed weights in memory (SRC k-groups per block, first
+// kg0): the same sums in the same order.
+template <int NB, int SRC>
+__device__ __forceinline__ void tf_gemm_mem(const uint4* __restrict__ W, int kg0, const float4 (&X)[NB],
+                                            floatx4 (&acc)[NB], int lane) {
+  const float4* Wl = reinterpret_cast<const float4*>(W) + kg0 * 64 + lane;
+#pragma unroll
+  for (int cb = 0; cb < NB; ++cb) acc[cb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kg = 0; kg < NB; ++kg) {
+    float4 w[NB];
+#pragma unroll
+    for (int cb = 0; cb < NB; ++cb) w[cb] = Wl[(cb * SRC + kg) * 64];
+    const float x[4] = {X[kg].x, X[kg].y, X[kg].z, X[kg].w};
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int cb = 0; cb < NB; ++cb) {
+        const float wr[4] = {w[cb].x, w[cb].y, w[cb].z, w[cb].w};
+        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[r], x[r], acc[cb], 0, 0, 0);
+      }
+  }
+}
+
 // The same with W^T, from the same LDS copy of W: output block cb takes
 // W[16 kg + 4 q + r][16 cb + i], element i % 4 of the slot of lane
 // (4 q + r, i / 4) in block (kg, cb).  tb[r] is that element's index in a block.
@@ -290,8 +314,11 @@ struct TfFwdLay {
 // the vector instructions between the products, 1.99 ms for the streaming
 // kernel, which applies the whole 3L x L first Linear per edge).  P_r may share its rows with a.agg: a
 // receiver's row is read with its edges' tiles and its sum stored after them,
-// by the same wave.
-template <int L, int D, bool SPLIT>
+// by the same wave.  HS: there are no P_s rows of the halo (ps_halo null, a
+// workspace without room for them); a tile with halo senders forms its own, the
+// same bits, with W_s from L2 (270,000 owned and 30,000 halo nodes, 3.7M edges,
+// two blocks at l = 128: 9.25 ms against 6.55 with the rows).
+template <int L, int D, bool SPLIT, bool HS>
 __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int64_t n_edges, int nact) {
   using Lay = TfFwdLay<L, D>;
   constexpr int NB = Lay::NB;
@@ -344,11 +371,23 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
     const bool ok = e < n;
     const RsMeta mt = tf_meta_make(cur, n);
     float4 ps[NB], pr[NB];
-    tf_load<NB>(mt.s < a.n_owned ? a.ps + (int64_t)mt.s * L : a.ps_halo + ((int64_t)mt.s - a.n_owned) * L, q, ps);
+    const bool far = mt.s >= a.n_owned;
+    const int64_t hrow = ((int64_t)mt.s - a.n_owned) * L;
+    // HS: a halo sender's latents in the place of its P_s (other rows of the
+    // product are not used)
+    tf_load<NB>(far ? (HS ? a.H : a.ps_halo) + hrow : a.ps + (int64_t)mt.s * L, q, ps);
     tf_load<NB>(a.pr + (int64_t)mt.r * L, q, pr);
     cur = tf_meta_load(a.erecv, a.send, sb + 16, E1, rg.past);
     __builtin_amdgcn_sched_barrier(0);
     floatx4 acc[NB];
+    if constexpr (HS) {
+      if (__ballot(far)) {
+        tf_gemm_mem<NB, 3 * NB>(a.mlp.lin[0].wf, NB, ps, acc, ln);
+#pragma unroll
+        for (int cb = 0; cb < NB; ++cb)
+          if (far) ps[cb] = make_float4(acc[cb][0], acc[cb][1], acc[cb][2], acc[cb][3]);
+      }
+    }
     tf_gemm<NB>(W1, ef, acc, slot);
     float4 h[NB];
 #pragma unroll
@@ -1268,11 +1307,11 @@ void allow_lds(F* fn, int bytes) {
 // workgroup) left some waves two tiles: forward 27.8 us.
 int tf_waves(int64_t edges) { return edges <= (int64_t)4 * RS_GRID * 11 ? 4 : TF_NWV; }
 
-template <int L, int D, bool SPLIT>
+template <int L, int D, bool SPLIT, bool HS>
 hipError_t edge_fwd_f32_t(const EdgeFwdArgs& a, int64_t n_edges, hipStream_t st) {
   using Lay = TfFwdLay<L, D>;
-  allow_lds(edge_fwd_f32_kernel<L, D, SPLIT>, Lay::END);
-  hipLaunchKernelGGL((edge_fwd_f32_kernel<L, D, SPLIT>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
+  allow_lds(edge_fwd_f32_kernel<L, D, SPLIT, HS>, Lay::END);
+  hipLaunchKernelGGL((edge_fwd_f32_kernel<L, D, SPLIT, HS>), dim3(RS_GRID), dim3(TF_NTH), Lay::END, st, a,
                      n_edges, tf_waves(n_edges));
   return hipGetLastError();
 }
@@ -1409,10 +1448,14 @@ bool edge_f32(int prec, int L, int D) { return prec == F32 && (L == 64 || (L == 
 
 hipError_t launch_edge_fwd_f32(int L, int D, const EdgeFwdArgs& a, int64_t n_edges, int64_t max_degree,
                                hipStream_t st) {
-  const bool split = tf_split(n_edges, max_degree);
-#define EF(LL, DD) \
-  if (L == LL && D == DD) \
-    return split ? edge_fwd_f32_t<LL, DD, true>(a, n_edges, st) : edge_fwd_f32_t<LL, DD, false>(a, n_edges, st);
+  const bool split = tf_split(n_edges, max_degree), hs = !a.ps_halo && a.H;
+#define EF(LL, DD)                                                            \
+  if (L == LL && D == DD) {                                                   \
+    if (hs) return split ? edge_fwd_f32_t<LL, DD, true, true>(a, n_edges, st) \
+                         : edge_fwd_f32_t<LL, DD, false, true>(a, n_edges, st); \
+    return split ? edge_fwd_f32_t<LL, DD, true, false>(a, n_edges, st)        \
+                 : edge_fwd_f32_t<LL, DD, false, false>(a, n_edges, st);      \
+  }
   EF(64, 2) EF(64, 3) EF(128, 2)
 #undef EF
   return hipErrorInvalidValue;

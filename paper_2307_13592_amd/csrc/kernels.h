@@ -41,8 +41,8 @@ struct EdgeFwdArgs {
   void* Eout;       // edge latents out, or null (last block)
   float* agg;       // [n_owned][L]
   const float* proj;  // node projections [n_local][2L] (row-split kernels), else unused
-  // fp32 row-split kernels: P_s of the owned and of the halo rows, P_r of the
-  // owned rows (may share its rows with agg); null: the streaming kernel
+  // fp32 row-split kernels: P_s of the owned and of the halo rows (null: formed
+  // per tile from H), P_r of the owned rows (may share its rows with agg)
   const float *ps, *ps_halo, *pr;
   void* hid_out;      // streaming and row-split kernels: the first Linear's ReLU output [E][L] (storage type) kept for the
                       // backward, or null

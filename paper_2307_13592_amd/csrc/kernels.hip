@@ -6014,8 +6014,7 @@ hipError_t launch_edge_fwd(int prec, int L, int D, const EdgeFwdArgs& a, int gri
   }
 #define EF(PP, LL, DD) \
   if (prec == PP && L == LL && D == DD) return edge_fwd_t<PP, LL, DD>(a, grid, st);
-  EF(F32, 64, 2) EF(F32, 64, 3) EF(F32, 128, 2) EF(F32, 128, 3) EF(F32, 256, 2) EF(F32, 256, 3)
-  EF(BF16, 128, 3)
+  EF(F32, 128, 3) EF(F32, 256, 2) EF(F32, 256, 3) EF(BF16, 128, 3)
 #undef EF
   return hipErrorInvalidValue;
 }

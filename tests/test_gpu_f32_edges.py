@@ -33,9 +33,9 @@ def test_ranges(l, D, edges):
 
 def test_static_workspace_limit():
     """A graph whose forward-only plan fits the static workspace only without
-    the halo rows of the projections runs (on the streaming kernel) and gives
-    the training plan's outputs to fp32 accuracy (1e-5: the kernels order the
-    first Linear's sums differently, a few roundings of 2^-24 each)."""
+    the halo rows of the projections runs without them and gives the training
+    plan's outputs to fp32 accuracy (1e-5; the latents of the nodes cut off come
+    from a float64 encoder here)."""
     say("[f32] static workspace limit")
     mesh = meshes.sector(30, 40, 40, 2, seed=5)
     c = local_inputs(mesh, 0, 128, 1, 2, 3)
