@@ -1345,9 +1345,9 @@ hipError_t node_proj_f32_t(const float* V, const float* H, int64_t n_owned, int6
                        n_halo, w1, ps, ps_halo, pr);
     return hipGetLastError();
   }
-  const int64_t g = (tiles + 7) / 8 * 16;  // both sides, multiples of 8 workgroups each
-  hipLaunchKernelGGL((node_proj_f32_kernel<L>), dim3((unsigned)(g < 512 ? g : 512)), dim3(TF_NTH), L * L * 4, st, V, H,
-                     n_owned, n_halo, w1, ps, ps_halo, pr);
+  // both sides: 256 workgroups each, two to a CU
+  hipLaunchKernelGGL((node_proj_f32_kernel<L>), dim3(2 * RS_GRID), dim3(TF_NTH), L * L * 4, st, V, H, n_owned, n_halo,
+                     w1, ps, ps_halo, pr);
   return hipGetLastError();
 }
 

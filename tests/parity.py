@@ -81,6 +81,25 @@ def local_inputs(mesh, p, latent, K, depth, seed, part=None):
     return dict(g=g, shapes=shapes, params=params, nf=nf, ef=ef, halo=halo, d_out=d_out, part=part)
 
 
+def away_from_zero(c, depth, shift=40.0, seed=1):
+    """The case with every ReLU input far from zero: each hidden Linear's biases
+    moved by +-shift at random, the weights after it cleared of what the open
+    units' shift adds (their mean over those units).  No unit changes sides for
+    float32 rounding then, so gradients of a float32 implementation stay within
+    rounding error of float64's at any size."""
+    params = c["params"].copy()
+    rng = np.random.default_rng(seed)
+    sl = dict(segments(c["shapes"]))
+    shapes = {name: shape for name, _, shape in c["shapes"]}
+    for name in [n[:-len(".lin0.W")] for n in shapes if n.endswith(".lin0.W")]:
+        for j in range(depth - 1):
+            sign = np.where(rng.random(shapes[f"{name}.lin{j}.b"][0]) < 0.5, -1.0, 1.0)
+            params[sl[f"{name}.lin{j}.b"]] += shift * sign
+            W = params[sl[f"{name}.lin{j + 1}.W"]].reshape(shapes[f"{name}.lin{j + 1}.W"])
+            W[:, sign > 0] -= W[:, sign > 0].mean(1, keepdims=True)
+    return dict(c, params=params)
+
+
 def run_gpu(c, latent, K, depth, prec, d_out=None, recompute=0, chunk_edges=0, h1_stash=0):
     s = Session(latent, K, depth, prec, c["g"], c["nf"], c["ef"], c["halo"], c["params"], recompute=recompute,
                 chunk_edges=chunk_edges, h1_stash=h1_stash)

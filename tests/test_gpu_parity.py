@@ -81,9 +81,10 @@ def test_sector_medium_l256():
 
 @pytest.mark.parametrize("prec", ["fp32", "bf16"])
 def test_sector_medium(prec):
-    """A partition large enough (>= 8192 edge and node rows) for the
+    """A partition large enough (>= 8192 edge and node rows) for the bf16
     register-resident weight-gradient kernels, which smaller cases do not
-    reach; halo on both sides."""
+    reach (fp32 takes them from 262,144 rows on: test_gpu_many_rows), and for
+    the fp32 node kernels over many rows; halo on both sides."""
     _case("sector 40x16x60 p1", meshes.sector(40, 16, 60, 4, seed=9), 1, 128, 2, 2, prec)
 
 
