@@ -1,0 +1,122 @@
+"""Encoders at every kind of feature width: at and around the widths where the
+kernels change (4 and 16 features in fp32, 4 in bf16), the smallest and the
+largest (1, 32), and the l = 256 layer passes; one block, every tensor against
+the oracle: in fp32 within the nominal 1e-4, with ReLU inputs away from zero; in
+bf16 the outputs and the encoders' tensors as in test_gpu_parity (the other
+tensors do not depend on the widths, and one of them on so few rows is a matter
+of single roundings: 2.003e-2 against its bound of 2e-2 in one case).  Feature
+arrays aligned to 4 bytes only give the same bits as aligned ones."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+import paper_2307_13592_amd as mgn
+from paper_2307_13592_amd.runner import Session
+from parity import away_from_zero, compare, say
+from synth import meshes
+import torch_ref
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(m, l, D, fins, seed=3):
+    g = mgn.mgn_graph_build(m.send, m.recv, np.zeros(m.n_nodes, np.int32), m.n_nodes, 0)
+    shapes = synth.param_shapes(l, 1, D, *fins)
+    rng = np.random.default_rng([seed, *fins])
+    return dict(g=g, shapes=shapes, params=synth.init_params(shapes, seed),
+                nf=rng.standard_normal((g["n_owned"], fins[0])).astype(np.float32),
+                ef=rng.standard_normal((g["n_edges"], fins[1])).astype(np.float32),
+                d_out=rng.standard_normal((g["n_owned"], 5)).astype(np.float32))
+
+
+def _step(c, l, D, prec, fins, unaligned=False, **plan):
+    s = Session(l, 1, D, prec, c["g"], c["nf"], c["ef"], None, c["params"], node_in=fins[0], edge_in=fins[1], **plan)
+    try:
+        if unaligned:
+            for k in ("node_feat", "edge_feat"):
+                t = getattr(s, k)
+                u = torch.empty(t.numel() + 1, device=t.device)[1:].view(t.shape)
+                assert u.data_ptr() % 16 == 4
+                setattr(s, k, u.copy_(t))
+        out = s.forward().cpu().numpy().copy()
+        dp = s.backward(c["d_out"])[0].cpu().numpy().copy()
+    finally:
+        s.close()
+    return out, dp, np.zeros((1, 0, l), np.float32)
+
+
+def _oracle(c, l, D, prec, fins, nf=None, ef=None):
+    cfg = oracle.ModelCfg(l, 1, D, node_in=fins[0], edge_in=fins[1], bf16=prec == "bf16")
+    f = lambda a: np.asarray(a, np.float64)
+    return oracle.step(cfg, c["g"], f(c["params"]), f(c["nf"] if nf is None else nf), f(c["ef"] if ef is None else ef),
+                       None, f(c["d_out"]))
+
+
+def _check(m, l, D, prec, fins):
+    say(f"[widths] {prec} l={l} D={D} {fins[0]} node, {fins[1]} edge features")
+    c = _inputs(m, l, D, fins)
+    if prec == "fp32":
+        c = away_from_zero(c, D)
+    gpu = _step(c, l, D, prec, fins)
+    assert all(np.isfinite(x).all() for x in gpu)
+    sens = cal = None
+    if prec == "bf16":
+        sens, cal = [], []
+        for i in range(5):
+            nf, ef = (c["nf"], c["ef"]) if i == 0 else synth.perturbed((c["nf"], c["ef"]), i, 2.0 ** -20)
+            if i > 0:
+                r = _oracle(c, l, D, prec, fins, nf, ef)
+                sens.append((r["out"], r["d_params"], r["d_halo"]))
+            cal.append(_torch(c, l, D, fins, nf, ef))
+    bad = compare(f"widths l={l} D={D} {fins}", prec, c["shapes"], gpu, _oracle(c, l, D, prec, fins), cal, sens=sens)
+    if prec == "bf16":
+        bad = [b for b in bad if b[0] == "out" or b[0].startswith("enc_")]
+    assert not bad, bad
+
+
+def _torch(c, l, D, fins, nf, ef):
+    """The independent float32 implementation with bf16 operands."""
+    model = torch_ref.TorchMGN(l, 1, D, *fins, dtype=torch.float32)
+    model.load_flat(c["params"], c["shapes"])
+    f = lambda a: torch.as_tensor(np.asarray(a, np.float32))
+    out = model(c["g"], f(nf), f(ef), torch.zeros(1, 0, l), bf16=True)
+    out.backward(f(c["d_out"]))
+    return out.detach().numpy(), model.flat_grad().numpy(), np.zeros((1, 0, l))
+
+
+F32 = [(64, 2, (4, 1)), (64, 2, (16, 3)), (64, 3, (17, 5)), (64, 2, (32, 16)), (64, 3, (1, 17)), (64, 2, (32, 32)),
+       (128, 2, (4, 3)), (128, 2, (16, 5)), (128, 2, (17, 16)), (128, 2, (32, 17)), (128, 3, (16, 3)),
+       (128, 3, (17, 5)), (128, 3, (4, 17)), (256, 2, (32, 17))]
+BF16 = [(64, 2, (4, 1)), (64, 3, (17, 5)), (64, 2, (32, 32)), (128, 2, (4, 3)), (128, 2, (17, 5)), (128, 2, (32, 32)),
+        (128, 3, (16, 17)), (256, 2, (32, 3)), (256, 3, (17, 4))]
+
+
+@pytest.mark.parametrize("l,D,fins", F32)
+def test_fp32(l, D, fins):
+    _check(meshes.hex_lattice(7), l, D, "fp32", fins)
+
+
+@pytest.mark.parametrize("l,D,fins", BF16)
+def test_bf16(l, D, fins):
+    _check(meshes.hex_lattice(7), l, D, "bf16", fins)
+
+
+def test_wide_node_encoder():
+    """Node rows in layer passes (35,937 nodes, few edges), 32 features."""
+    m = meshes.hex_lattice(33)
+    keep = np.random.default_rng(1).choice(m.n_edges, 3001, replace=False)
+    keep.sort()
+    m.send, m.recv = m.send[keep], m.recv[keep]
+    _check(m, 256, 2, "bf16", (32, 4))
+
+
+@pytest.mark.parametrize("prec,l,D,fins", [("fp32", 64, 2, (11, 8)), ("fp32", 128, 2, (16, 4)), ("fp32", 64, 2, (20, 24)),
+                                           ("bf16", 64, 3, (12, 4)), ("bf16", 128, 2, (11, 8)), ("bf16", 256, 2, (8, 4))])
+def test_unaligned_features(prec, l, D, fins):
+    say(f"[widths] unaligned {prec} l={l} D={D} {fins}")
+    c = _inputs(meshes.hex_lattice(7), l, D, fins)
+    want, got = _step(c, l, D, prec, fins), _step(c, l, D, prec, fins, unaligned=True)
+    assert np.isfinite(want[0]).all() and np.isfinite(want[1]).all()
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])

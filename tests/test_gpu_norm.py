@@ -56,3 +56,26 @@ def test_norm_reproducible_and_degenerate():
     fresh = Normalizer(11, "cuda:0")
     xt = torch.as_tensor(x[:100]).cuda()
     assert torch.equal(fresh.apply(xt), xt)
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (3, 4), (1023, 11), (4097, 3), (700, 64)])
+def test_norm_unaligned(rows, cols):
+    """Arrays aligned to 4 bytes only (x, out, or both) give the same bits."""
+    print(f"[norm] unaligned {rows} x {cols}", flush=True)
+    x = torch.as_tensor((3 + 2 * np.random.default_rng(rows).standard_normal((rows, cols))).astype(np.float32)).cuda()
+
+    def at(offset):
+        return torch.full((rows * cols + 8,), float("nan"), device="cuda")[offset:offset + rows * cols].view(rows, cols)
+
+    n = Normalizer(cols)
+    n.accumulate(x)
+    want = n.apply(x)
+    for xo, oo in ((1, 0), (0, 1), (2, 3), (3, 3)):
+        y, out = at(xo).copy_(x), at(oo)
+        n2 = Normalizer(cols)
+        n2.accumulate(y)
+        assert torch.equal(n2.stats, n.stats)
+        n2.apply(y, out)
+        assert torch.equal(out, want), (xo, oo)
+        n2.apply(y, y)
+        assert torch.equal(y, want), "in place"
