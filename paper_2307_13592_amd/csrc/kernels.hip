@@ -5743,11 +5743,11 @@ bool rows_rt(int prec, int L, int D, int kind) {
   return prec == BF16 && D == 2 && (L == 64 || L == 128) && kind != DECODER;
 }
 
-bool rows_rw(int prec, int L, int D, int kind) {
-  return prec == BF16 && L == 256 && (D == 2 || D == 3) && (kind == NODE_BLOCK || kind == ENC_EDGE);
+bool rows_rw(int prec, int L, int D, int kind, int fin) {
+  return prec == BF16 && L == 256 && (D == 2 || D == 3) && (kind == NODE_BLOCK || (kind == ENC_EDGE && fin <= RW_ENC_FIN));
 }
 
-bool rows_keep_h1(int prec, int L, int D) { return rows_rt(prec, L, D, NODE_BLOCK) || rows_rw(prec, L, D, NODE_BLOCK); }
+bool rows_keep_h1(int prec, int L, int D) { return rows_rt(prec, L, D, NODE_BLOCK) || rows_rw(prec, L, D, NODE_BLOCK, 0); }
 
 template <int D>
 static hipError_t rows_rw_fwd_t(const RowsFwdArgs& a, hipStream_t st) {
@@ -5814,14 +5814,14 @@ static_assert((int64_t)RS_GRID * RtRowsLay<128, ENC_EDGE>::NWV * 128 * RtRowsLay
 int rows_rt_w1_parts(int prec, int L, int D, int kind, int fin, int64_t rows) {
   if (kind != ENC_EDGE || fin < 1 || rows_wide(prec, L, D, kind, rows)) return 0;
   if (rows_f32(prec, L, D, kind, fin)) return rows_f32_w1_parts(rows, kind, fin);
-  if (rows_rw(prec, L, D, kind)) return fin <= RW_ENC_FIN ? RS_GRID * RwEncBwdLay<3>::NWV : 0;
+  if (rows_rw(prec, L, D, kind, fin)) return RS_GRID * RwEncBwdLay<3>::NWV;
   if (!rows_rt(prec, L, D, kind) || fin > RtRowsLay<128, ENC_EDGE>::W1_FIN) return 0;
   return RS_GRID * RtRowsLay<128, ENC_EDGE>::NWV;
 }
 
 hipError_t launch_rows_fwd(int prec, int L, int D, int kind, const RowsFwdArgs& a, hipStream_t st) {
   if (rows_fwd_f32(prec, L, D, kind, a.fin)) return launch_rows_fwd_f32(L, D, kind, a, st);
-  if (rows_rw(prec, L, D, kind)) {
+  if (rows_rw(prec, L, D, kind, a.fin)) {
     if (kind == ENC_EDGE) return D == 2 ? rows_rw_enc_fwd_t<2>(a, st) : rows_rw_enc_fwd_t<3>(a, st);
     return D == 2 ? rows_rw_fwd_t<2>(a, st) : rows_rw_fwd_t<3>(a, st);
   }
@@ -5876,7 +5876,8 @@ static int rows_bwd_tile(int kind) {
 int rows_bwd_grid(int prec, int L, int D, int kind, int fin, int64_t rows, int grid) {
   if (rows_f32(prec, L, D, kind, fin)) return rows_f32_grid(rows);
   if (rows_wide(prec, L, D, kind, rows)) return RS_GRID;
-  if (rows_rs(prec, L, D, kind) || rows_rt_bwd(prec, L, D, kind, false) || rows_rw(prec, L, D, kind)) return RS_GRID;
+  if (rows_rs(prec, L, D, kind) || rows_rt_bwd(prec, L, D, kind, false) || rows_rw(prec, L, D, kind, fin))
+    return RS_GRID;
   int tm = 16;
 #define RG(PP, LL, DD) \
   if (prec == PP && L == LL && D == DD) tm = rows_bwd_tile<PP, LL, DD>(kind);
@@ -5898,7 +5899,7 @@ static hipError_t rows_bwd_rs_t(const RowsBwdArgs& a, hipStream_t st) {
 hipError_t launch_rows_bwd(int prec, int L, int D, int kind, const RowsBwdArgs& a, int grid, hipStream_t st) {
   if (rows_f32(prec, L, D, kind, a.fin)) return launch_rows_bwd_f32(L, D, kind, a, st);
   if (rows_wide(prec, L, D, kind, a.rows)) return launch_rows_bwd_wide(D, kind, a, st);
-  if (rows_rw(prec, L, D, kind)) {
+  if (rows_rw(prec, L, D, kind, a.fin)) {
     if (kind == ENC_EDGE) return D == 2 ? rows_rw_enc_bwd_t<2>(a, st) : rows_rw_enc_bwd_t<3>(a, st);
     return D == 2 ? rows_rw_bwd_t<2>(a, st) : rows_rw_bwd_t<3>(a, st);
   }

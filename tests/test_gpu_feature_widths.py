@@ -90,7 +90,7 @@ F32 = [(64, 2, (4, 1)), (64, 2, (16, 3)), (64, 3, (17, 5)), (64, 2, (32, 16)), (
        (128, 2, (4, 3)), (128, 2, (16, 5)), (128, 2, (17, 16)), (128, 2, (32, 17)), (128, 3, (16, 3)),
        (128, 3, (17, 5)), (128, 3, (4, 17)), (256, 2, (32, 17))]
 BF16 = [(64, 2, (4, 1)), (64, 3, (17, 5)), (64, 2, (32, 32)), (128, 2, (4, 3)), (128, 2, (17, 5)), (128, 2, (32, 32)),
-        (128, 3, (16, 17)), (256, 2, (32, 3)), (256, 3, (17, 4))]
+        (128, 3, (16, 17)), (256, 2, (32, 3)), (256, 3, (17, 4)), (256, 2, (16, 5)), (256, 3, (4, 32))]
 
 
 @pytest.mark.parametrize("l,D,fins", F32)
@@ -101,6 +101,11 @@ def test_fp32(l, D, fins):
 @pytest.mark.parametrize("l,D,fins", BF16)
 def test_bf16(l, D, fins):
     _check(meshes.hex_lattice(7), l, D, "bf16", fins)
+
+
+def test_wide_edge_encoder():
+    """Edge rows in layer passes (33,048 edges), 9 features."""
+    _check(meshes.hex_lattice(18), 256, 2, "bf16", (11, 9))
 
 
 def test_wide_node_encoder():
