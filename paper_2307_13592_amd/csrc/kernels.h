@@ -66,7 +66,7 @@ struct RowsBwdArgs {
   float* vpart;      // [grid][nvec] per-workgroup bias / LayerNorm gradients
   int nvec;
   float eps;
-  float* w1_part;    // ENC_EDGE, T-form kernel: when set, per-wave partials [waves][L][fin] of the
+  float* w1_part;    // ENC_EDGE, T-form kernel: when set, partials [rows_rt_w1_parts][L][fin] of the
                      // first Linear's weight gradient instead of storing delta[0] (rows_rt_w1_parts)
 };
 
@@ -217,9 +217,10 @@ hipError_t launch_rows_bwd(int prec, int L, int D, int kind, const RowsBwdArgs& 
 // Workgroups (= vector-partial slots) launch_rows_bwd uses for `rows` rows when
 // asked for at most `grid`.
 int rows_bwd_grid(int prec, int L, int D, int kind, int fin, int64_t rows, int grid);
-// Number of per-wave partials (RowsBwdArgs::w1_part) with which the backward
-// of `kind` forms its first Linear's weight gradient itself, or 0 if it
-// stores delta[0] for a separate weight-gradient GEMM instead.
+// Number of partials (RowsBwdArgs::w1_part; one per wave, in fp32 one per
+// workgroup) with which the backward of `kind` forms its first Linear's weight
+// gradient itself, or 0 if it stores delta[0] for a separate weight-gradient
+// GEMM instead.
 int rows_rt_w1_parts(int prec, int L, int D, int kind, int fin, int64_t rows);
 hipError_t launch_edge_bwd(int prec, int L, int D, const EdgeBwdArgs& a, int grid, hipStream_t st);
 // Workgroups (= vector-partial slots) the edge backward uses when asked for `grid`.
@@ -258,7 +259,10 @@ hipError_t launch_node_proj_r(int L, const void* v16, int64_t n_owned, const Lin
 bool edge_rsb(int prec, int L, int D);
 // bf16, l = 256, from WIDE_ROWS rows on: the backward of the edge half, the
 // node half and the encoders as one launch per Linear (wide.hip).  The edge
-// encoder then stores delta[0].
+// encoder then stores delta[0].  The line is on the safe side of the crossover,
+// which lies under 10,000 rows (one-block steps, depth 2, passes against fused:
+// 8,368 edges 386 and 402 us, 26,856 457 and 527, 62,048 632 and 750, 2.0M 10.0
+// and 13.5 ms).
 constexpr int64_t WIDE_ROWS = 32768;
 bool edge_wide(int prec, int L, int D, int64_t edges);
 hipError_t launch_edge_bwd_wide(int D, const EdgeBwdArgs& a, int64_t rows, hipStream_t st);
@@ -283,7 +287,8 @@ hipError_t launch_dw_stream(const DwArgs& a, float* dst, int ldw, int accumulate
 bool dw_stream_quad_ok(int prec, const DwArgs& a);
 hipError_t launch_dw_stream_quad(const DwArgs& a, float* dst, int ldw, int accumulate, hipStream_t st);
 // The same for fp32 layers with 128 inputs and 128 outputs (dw_stream_f32_ok):
-// wave partials in plain [o][i] order, then the fixed-order split reduction.
+// one partial per workgroup in plain [o][i] order, then the fixed-order split
+// reduction.
 bool dw_stream_f32_ok(int prec, const DwArgs& a);
 hipError_t launch_dw_stream_f32(const DwArgs& a, float* dst, int ldw, int accumulate, hipStream_t st);
 // All jobs and vectors of g (two launches); g's split fields are set here.

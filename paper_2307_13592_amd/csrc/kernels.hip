@@ -5477,9 +5477,8 @@ __global__ __launch_bounds__(DWS_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) 
           }
 }
 
-// dst[o * ldw + i] (+)= sum over the S wave partials, in wave order within
-// each of four interleaved sets, combined in set order; entry x of a partial
-// is (j, j', lane, r) -> o = 8 (4 (lane >> 4) + r) + j, i = 8 (lane & 15) + j'.
+// dst[o * ldw + i] (+)= sum over the S partials, in their order within each of
+// four interleaved sets, combined in set order; entry x of a partial is (j, j', lane, r) -> o = 8 (4 (lane >> 4) + r) + j, i = 8 (lane & 15) + j'.
 // gridDim.y > 1: quadrant y = blockIdx.y of a 256 x 256 gradient, its S
 // partials from part + y S 16384, its outputs at rows 128 (y >> 1) and
 // columns 128 (y & 1) on.
@@ -6110,7 +6109,11 @@ hipError_t launch_input_grad(int prec, int L, const InGradArgs& a, hipStream_t s
 int dw_stream_parts() { return DWS_WAVES; }
 
 // Rows from which an fp32 128 x 128 layer takes a launch of its own: there the
-// single read of each operand outweighs its 64 MiB of partials.
+// single read of each operand outweighs its 16 MiB of partials and the launches.
+// All weight gradients of a one-block step, this kernel for the edge layers
+// against the group: l = 128, 119,000 edges 269 and 216 us, 258,000 413 and 386,
+// 507,000 660 and 691, 2.0M 2.17 and 2.61 ms; l = 256, 258,000 edges 1.58 and
+// 1.47 ms, 507,000 2.66 and 2.91.
 constexpr int64_t DWS_F32_ROWS = 1 << 18;
 
 bool dw_stream_f32_ok(int prec, const DwArgs& a) {
