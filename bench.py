@@ -102,8 +102,9 @@ def algorithmic(timer: str, cfg, E: int, No: int, Nh: int, lean: bool = False, s
 def step_roofline(cfg, E: int, No: int, ms: float) -> dict:
     """Position of the whole step against the work the method needs per
     edge-block, for kernels that fuse gather, MLP and scatter: flops per
-    edge-block forward 2l^2(D+2) + 2l^2(D+1) No/E, forward + backward with
-    recompute 4x that; HBM bytes per edge-block forward 2 l s_e + 4, backward
+    edge-block forward 2 l^2 D + (2 * 2 l^2 + 2 l^2 (D+1)) No/E (the edge MLP's
+    sender and receiver columns once per node), forward + backward without
+    recompute 3x that; HBM bytes per edge-block forward 2 l s_e + 4, backward
     l s_e + 4 l s_g + 8 (s_e: bytes of a stored edge latent, s_g: of a
     stored edge gradient, both 2 in bf16, 4 in fp32), plus per node and
     block 40 l bytes (forward: v read, agg
@@ -112,7 +113,7 @@ def step_roofline(cfg, E: int, No: int, ms: float) -> dict:
     the larger of flops / matrix peak and bytes / HBM peak."""
     l, D, K = cfg.latent, cfg.depth, cfg.K
     se = 2 if cfg.precision == "bf16" else 4
-    fl = 4 * (2 * l * l * (D + 2) + 2 * l * l * (D + 1) * No / E)
+    fl = 3 * (2 * l * l * D + (2 * 2 * l * l + 2 * l * l * (D + 1)) * No / E)
     by = (2 * l * se + 4) + (l * se + 4 * l * se + 8) + 40 * l * No / E
     peak_flops = PEAK["bf16"] if cfg.precision == "bf16" else PEAK["fp32"]
     t_fl, t_by = fl * E * K / peak_flops, by * E * K / PEAK["hbm"]
@@ -241,12 +242,16 @@ def main():
     peak_flops = PEAK["bf16"] if cfg.precision == "bf16" else PEAK["fp32"]
     kroofs = {}
     for k, (t, n) in timers.items():
-        alg = algorithmic(k, cfg, ne, no, nh, lean=recompute > 0, stash=stash) if n else None
+        # (checkpointing: of a block's projections only those before its edge
+        # backward have the sender half, as with the stash)
+        half = 1 - cfg.K * k_steps / n if n and k == "node_proj" and recompute > 0 else stash
+        alg = algorithmic(k, cfg, ne, no, nh, lean=recompute > 0, stash=half) if n else None
         if alg is None:
             continue
-        # a block's edge backward may run as several receiver chunks
-        # (checkpointed plan): one launch then does its share of the block
-        share = cfg.K * k_steps / n if k == "edge_bwd" else 1.0
+        # a block's edge backward and its sender sums may run as several
+        # receiver chunks (checkpointed plan): one launch then does its share
+        # of the block
+        share = cfg.K * k_steps / n if k in ("edge_bwd", "input_grad") else 1.0
         by, fl = alg[0] * share, alg[1] * share
         t_launch = t / n * 1e-3
         if fl / by >= peak_flops / PEAK["hbm"]:

@@ -57,6 +57,13 @@ def test_step_roofline_fraction():
     assert r["frac"] == pytest.approx(r["roof_ms"] / 400.0)
     # at the roof the fraction is one
     assert bench.step_roofline(cfg, E, NO, r["roof_ms"])["frac"] == pytest.approx(1.0)
+    # a measured step is above its roof: C3 (fp32), 561.6 ms, bound by 3x the
+    # forward's products with the node columns of the edge MLP once per node
+    c3 = synth.CONFIGS["C3"]
+    r = bench.step_roofline(c3, 13_824_680, 1_000_000, 561.6)
+    products = 3 * 2 * 128 * 128 * (2 * 13_824_680 + (2 + 3) * 1_000_000) * 15
+    assert r["bound"] == "mfma" and r["roof_ms"] == pytest.approx(products / 157.3e12 * 1e3)
+    assert 0.5 < r["frac"] < 1
 
 
 def test_traffic_summary_used_only_for_its_kernels(tmp_path, monkeypatch):
