@@ -5478,7 +5478,8 @@ __global__ __launch_bounds__(DWS_NT) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 }
 
 // dst[o * ldw + i] (+)= sum over the S partials, in their order within each of
-// four interleaved sets, combined in set order; entry x of a partial is (j, j', lane, r) -> o = 8 (4 (lane >> 4) + r) + j, i = 8 (lane & 15) + j'.
+// four interleaved sets, combined in set order; entry x of a partial is (j, j',
+// lane, r) -> o = 8 (4 (lane >> 4) + r) + j, i = 8 (lane & 15) + j'.
 // gridDim.y > 1: quadrant y = blockIdx.y of a 256 x 256 gradient, its S
 // partials from part + y S 16384, its outputs at rows 128 (y >> 1) and
 // columns 128 (y & 1) on.
