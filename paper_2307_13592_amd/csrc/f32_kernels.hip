@@ -332,10 +332,10 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
   float* vbh = vbl + 3 * L;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  const RsEmpty empty = rs_empty_load(a.row_ptr, 0, a.n_owned);
   const TfRange rg = tf_range<SPLIT>(a.row_ptr, a.erecv, 0, n_edges, nact);
   const int64_t E0 = rg.E0, E1 = rg.E1;
   bool open = rg.open;
-  rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
   tf_copy_frags<NB, 3 * NB, TF_NTH>(W1, a.mlp.lin[0].wf, 0);
   if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
   tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
@@ -344,6 +344,7 @@ __global__ __launch_bounds__(TF_NTH) void edge_fwd_f32_kernel(EdgeFwdArgs a, int
   rt_copy_vec(vbt, a.mlp.beta, L);
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   __syncthreads();
+  rs_zero_empty(empty, a.row_ptr, a.agg, L);
   if (!SPLIT && E0 >= E1) return;
   const float* Ein = reinterpret_cast<const float*>(a.Ein);
   float* Eout = reinterpret_cast<float*>(a.Eout);
@@ -466,10 +467,10 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
   float* vbh = vbl + 2 * L;
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  const RsEmpty empty = rs_empty_load(a.row_ptr, a.r_lo, a.r_hi);
   const TfRange rg = tf_range<SPLIT>(a.row_ptr, a.erecv, a.e_base, n_edges, nact);
   const int64_t E0 = rg.E0, E1 = rg.E1;
   bool open = rg.open;
-  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
   tf_copy_frags<NB, NB, TF_NTH>(WL, a.mlp.lin[D - 1].wf, 0);
   if constexpr (D == 3) tf_copy_frags<NB, NB, TF_NTH>(WH, a.mlp.lin[1].wf, 0);
   tf_copy_frags<NB, NB, TF_NTH>(W1, a.mlp.lin[0].wb, 0);  // e block: the first NB column blocks
@@ -477,6 +478,7 @@ __global__ __launch_bounds__(TF_NTH) void edge_bwd_f32_kernel(EdgeBwdArgs a, int
   rt_copy_vec(vg, a.mlp.gamma, L);
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   __syncthreads();
+  rs_zero_empty(empty, a.row_ptr, a.dagg, L);
   // column totals of the bias / LayerNorm gradients (rt_col_totals' share of
   // each lane): gamma, beta, last bias, hidden biases
   constexpr int NQ = 2 + D;

@@ -1775,6 +1775,7 @@ __global__ __launch_bounds__((RsFwdLay<L, D>::NTH)) void edge_fwd_rs_kernel(Edge
   float* vbh = vbl + 3 * L;                                     // hidden bias (D = 3)
   const int wave = wave_id(), lane = threadIdx.x & 63;
   float* scr32 = reinterpret_cast<float*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  const RsEmpty empty = rs_empty_load(a.row_ptr, 0, a.n_owned);
   rs_copy_frags(W1, a.mlp.lin[0].wf, NB, NKH, 3 * NKH, 0);  // B operands read from memory rows
   rs_copy_frags(WS, a.mlp.lin[0].wf, NB, NKH, 3 * NKH, NKH);
   if constexpr (D == 3) rt_copy_frags(WH, a.mlp.lin[1].wf, NB, NKH, NKH, 0);
@@ -1786,7 +1787,7 @@ __global__ __launch_bounds__((RsFwdLay<L, D>::NTH)) void edge_fwd_rs_kernel(Edge
   __syncthreads();
   int64_t r0, r1;
   rs_range(a.row_ptr, 0, a.n_owned, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
+  rs_zero_empty(empty, a.row_ptr, a.agg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
   uint16_t* Eout = reinterpret_cast<uint16_t*>(a.Eout);
@@ -1954,6 +1955,7 @@ __global__ __launch_bounds__(RS_NTH) void edge_bwd_rs_kernel(EdgeBwdArgs a) {
   float* vbh = vbl + 2 * L;                                     // hidden bias (D = 3)
   const int wave = wave_id(), lane = threadIdx.x & 63;
   uint16_t* scr = reinterpret_cast<uint16_t*>(lds + Lay::OFF_SCR + wave * Lay::SCR);
+  const RsEmpty empty = rs_empty_load(a.row_ptr, a.r_lo, a.r_hi);
   rt_copy_vec(vbl, a.mlp.lin[D - 1].b, L);
   rt_copy_vec(vg, a.mlp.gamma, L);
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
@@ -1966,7 +1968,7 @@ __global__ __launch_bounds__(RS_NTH) void edge_bwd_rs_kernel(EdgeBwdArgs a) {
   __syncthreads();
   int64_t r0, r1;
   rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
+  rs_zero_empty(empty, a.row_ptr, a.dagg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);
   // column totals of the bias / LayerNorm gradients (rt_col_totals' share of
@@ -2498,6 +2500,7 @@ void edge_fwd_rw_kernel(EdgeFwdArgs a) {
     if (j == 0) rw_load<NTH, false>(st, src[0], c, vo_plain);
     else rw_load<NTH, true>(st, src[j == D - 1 ? 2 : 1], c, vo_perm);
   };
+  const RsEmpty empty = rs_empty_load(a.row_ptr, 0, a.n_owned);
   RwStage<NTH> stg;
   load(stg, 0);
   rw_store<NTH>(stg, buf);
@@ -2508,7 +2511,7 @@ void edge_fwd_rw_kernel(EdgeFwdArgs a) {
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   int64_t r0, r1;
   rs_range(a.row_ptr, 0, a.n_owned, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, 0, a.n_owned, a.agg, L);
+  rs_zero_empty(empty, a.row_ptr, a.agg, L);
   // wave-uniform bounds, kept in scalar registers
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);
   const int ntile = rw_max_tiles((int)((E1 - E0 + TE - 1) / TE), reinterpret_cast<int*>(lds + Lay::OFF_SLOT));
@@ -2781,6 +2784,7 @@ void edge_bwd_rw_kernel(EdgeBwdArgs a) {
       rw_load<NTH, true>(st, bsrc[layer == 0 ? 0 : (layer == D - 1 ? 2 : 1)], c, vo_perm);
     }
   };
+  const RsEmpty empty = rs_empty_load(a.row_ptr, a.r_lo, a.r_hi);
   RwStage<NTH> stg[2];  // chunks p + 1 and p + 2 in flight at step p
   load(stg[0], 0);
   rw_store<NTH>(stg[0], buf);
@@ -2791,7 +2795,7 @@ void edge_bwd_rw_kernel(EdgeBwdArgs a) {
   if constexpr (D == 3) rt_copy_vec(vbh, a.mlp.lin[1].b, L);
   int64_t r0, r1;
   rs_range(a.row_ptr, a.r_lo, a.r_hi, r0, r1, blockDim.x >> 6);
-  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.dagg, L);
+  rs_zero_empty(empty, a.row_ptr, a.dagg, L);
   const int64_t E0 = rs_uniform(a.row_ptr[r0]), E1 = rs_uniform(a.row_ptr[r1]);  // wave-uniform
   const int ntile = rw_max_tiles((int)((E1 - E0 + 15) / 16), reinterpret_cast<int*>(lds + Lay::OFF_SLOT));
   const uint16_t* Ein = reinterpret_cast<const uint16_t*>(a.Ein);

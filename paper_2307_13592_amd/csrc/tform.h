@@ -80,19 +80,35 @@ __device__ __forceinline__ void rs_range_e(const int32_t* __restrict__ row_ptr, 
   E1 = rs_uniform(E1);
 }
 
-// Zeroes the rows (width L) of the receivers in [lo_r, hi_r) without edges:
-// every wave an even share of the receivers, a lane per receiver.  (With each
-// wave zeroing between its own edges' receivers, a long run of receivers
-// without edges fell to one wave: 300,000 of them at l = 128 took 6.8 ms a
-// launch, now 0.064.)
-__device__ __forceinline__ void rs_zero_empty(const int32_t* __restrict__ row_ptr, int64_t lo_r, int64_t hi_r,
-                                              float* dst, int L) {
-  const int lane = threadIdx.x & 63, nwv = blockDim.x >> 6;
-  const int64_t q = (int64_t)blockIdx.x * nwv + wave_id(), W = (int64_t)gridDim.x * nwv, n = hi_r - lo_r;
-  const int64_t r1 = lo_r + n * (q + 1) / W;
-  for (int64_t r = lo_r + n * q / W + lane; r < r1; r += 64)
-    if (row_ptr[r] == row_ptr[r + 1])
-      for (int c = 0; c < L; c += 4) *reinterpret_cast<float4*>(dst + r * L + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+// Zeroes the rows (width L) of the receivers in [lo_r, hi_r) without edges: 64
+// receivers, a lane each, go to every wave in turn.  (With each wave zeroing
+// between its own edges' receivers, a long run of receivers without edges fell
+// to one wave: 300,000 of them at l = 128 took 6.8 ms a launch, now 0.064.)
+// rs_empty_load, at the kernel's start, loads the bounds of the lane's first
+// receiver, whose latency (1 us a launch on small graphs) then passes with the
+// weights' on their way to LDS.
+struct RsEmpty {
+  int64_t r, end;
+  int32_t a, b;
+};
+__device__ __forceinline__ RsEmpty rs_empty_load(const int32_t* __restrict__ row_ptr, int64_t lo_r, int64_t hi_r) {
+  RsEmpty z{lo_r + (int64_t)blockIdx.x * blockDim.x + threadIdx.x, hi_r, 0, 0};
+  if (z.r < z.end) {
+    z.a = row_ptr[z.r];
+    z.b = row_ptr[z.r + 1];
+  }
+  return z;
+}
+__device__ __forceinline__ void rs_zero_empty(RsEmpty z, const int32_t* __restrict__ row_ptr, float* dst, int L) {
+  while (z.r < z.end) {
+    if (z.a == z.b)
+      for (int c = 0; c < L; c += 4) *reinterpret_cast<float4*>(dst + z.r * L + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+    z.r += (int64_t)gridDim.x * blockDim.x;
+    if (z.r < z.end) {
+      z.a = row_ptr[z.r];
+      z.b = row_ptr[z.r + 1];
+    }
+  }
 }
 
 // One 16-edge tile's metadata, every lane for its row e = lane & 15: the

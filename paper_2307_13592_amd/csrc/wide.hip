@@ -311,11 +311,12 @@ __global__ __launch_bounds__(W_NTH) __attribute__((amdgpu_waves_per_eu(2, 2))) v
   uint4* W = reinterpret_cast<uint4*>(lds);
   const int wave = wave_id(), lane = threadIdx.x & 63;
   uint16_t* scr = reinterpret_cast<uint16_t*>(lds + W_OFF_SCR + wave * 2048);
+  const RsEmpty empty = rs_empty_load(a.row_ptr, a.r_lo, a.r_hi);
   int64_t E0, E1;
   rs_range_e(a.row_ptr, a.recv, a.e_lo, a.rows, W_NWV, wave, E0, E1);
-  rs_zero_empty(a.row_ptr, a.r_lo, a.r_hi, a.sum, WL);
   wide_copy<true>(W, a.w, a.src_nkg);
   __syncthreads();
+  rs_zero_empty(empty, a.row_ptr, a.sum, WL);
   if (E0 >= E1) return;
   float run[WL / 64] = {};
   RsMeta mt_next = rt_meta_make(rt_meta_load(a.recv, a.send, E0, E1));
