@@ -24,10 +24,10 @@ namespace mgn {
 namespace {
 
 // Waves per workgroup: two per SIMD.  The fp32 MFMA and the vector ALU take
-// turns (counters at l = 128: matrix pipe busy 69 % of the SIMD cycles, vector
-// instructions 20 % forward and 25 % backward, which add up to 90 and 94 %), so
+// turns (counters at l = 128: matrix pipe busy 70 % of the SIMD cycles, vector
+// instructions 20 % forward and 24 % backward, which add up to 90 and 94 %), so
 // more waves hide nothing more: at l = 128 they spill (12 waves: forward 1.03 ms,
-// backward 1.84 ms on 1.35M edges against 0.85 and 1.23), at l = 64 they cut the
+// backward 1.84 ms on 1.35M edges against 0.84 and 1.22), at l = 64 they cut the
 // ranges finer (16 waves: backward 113 us on 270,000 edges against 101).
 constexpr int TF_NWV = 8, TF_NTH = 64 * TF_NWV;
 
@@ -310,7 +310,7 @@ struct TfFwdLay {
 };
 
 // Forward of one block's edge half.  Bound by the matrix pipe: 4 L^2 flops per
-// edge at 157 TFLOP/s (L = 128, 1.35M edges: 0.56 ms; measured 0.85 ms with
+// edge at 157 TFLOP/s (L = 128, 1.35M edges: 0.56 ms; measured 0.84 ms with
 // the vector instructions between the products, 1.99 ms for the streaming
 // kernel, which applies the whole 3L x L first Linear per edge).  P_r may share its rows with a.agg: a
 // receiver's row is read with its edges' tiles and its sum stored after them,
@@ -448,7 +448,7 @@ struct TfBwdLay {
 };
 
 // Backward of one block's edge half, bound by the matrix pipe as the forward
-// (6 L^2 flops per edge; L = 128, 1.35M edges: floor 0.84 ms, measured 1.23 ms,
+// (6 L^2 flops per edge; L = 128, 1.35M edges: floor 0.84 ms, measured 1.22 ms,
 // the streaming kernel 3.15 ms with every weight fragment read from L2 for
 // each tile).  It starts from the forward's h_1 (a.hid_in): the
 // layers after the first recomputed, LayerNorm backward, the data gradients
