@@ -243,7 +243,7 @@ mgn_status mgn_forward(mgn_model* m, const mgn_graph* g, const float* node_feat,
  * capture, serving loops, harnesses that forbid hipMalloc): mgn_forward with
  * its workspace in a library-owned static device array of
  * MGN_NOALLOC_WS_MAX bytes, one per GPU, held until the process ends.  Same
- * arguments as mgn_forward without workspace / ws_bytes; same launches and
+ * arguments as mgn_forward without workspace / ws_bytes; same
  * results.  Allocates nothing (no hipMalloc, no events).  Errors:
  * MGN_E_NOMEM when mgn_workspace_size for (m, g) exceeds
  * MGN_NOALLOC_WS_MAX (nothing is enqueued); MGN_E_STATE when launch timing

@@ -13,7 +13,8 @@
 // column order (16 bytes per lane and 16-column block), and the accumulators,
 // which hold columns 16 cb + 4 q + r of row e and so are the next product's B
 // operand as they stand.  One wave works alone on 16-edge tiles of its own
-// receiver-aligned range; the per-edge weights sit in LDS.
+// receiver-aligned range (a very large receiver: of its share of a workgroup's,
+// tf_range); the per-edge weights sit in LDS.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
