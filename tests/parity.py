@@ -218,7 +218,7 @@ def compare(name, prec, shapes, gpu, ref, calib=None, halo_sel=None, calib_facto
     e = rel_err(out, ref["out"])
     rows.append(("out", e, None, None, tol))
     worst = ("out", e, tol)
-    if e > tol:
+    if not e <= tol:  # (a NaN fails)
         bad.append(("out", e, tol))
 
     def check(nm, got, want, cal, sen):
@@ -228,9 +228,9 @@ def compare(name, prec, shapes, gpu, ref, calib=None, halo_sel=None, calib_facto
         se = float(sen) if isinstance(sen, (float, np.floating)) else _max_err(sen, want)
         t = bound_of(prec, ce, se, calib_factor)
         rows.append((nm, e, ce, se, t))
-        if e / t > worst[1] / worst[2]:
+        if not e / t <= worst[1] / worst[2]:
             worst = (nm, e, t)
-        if e > t:
+        if not e <= t:
             bad.append((nm, e, t))
 
     stored = isinstance(sens, dict)
